@@ -82,9 +82,7 @@ __global__ __launch_bounds__(256) void ssq_kernel(const float* x, int d, float* 
   if (threadIdx.x == 0) ssq[t] = red[0];
 }
 
-void norm_rows_f32(const float* x, int M, int d, const float* g, float* xn, float* ssq, hipStream_t st) {
-  (void)g;
-  (void)xn;
+void norm_rows_f32(const float* x, int M, int d, float* ssq, hipStream_t st) {
   hipLaunchKernelGGL(ssq_kernel, dim3(M), dim3(256), 0, st, x, d, ssq);
 }
 

@@ -774,7 +774,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       EpiArgs e = base;
       e.kind = EPI_QKV;
       e.ssq = s->ssq;
-      e.ssq_parts = 1;
+      e.ssq_parts = ssq_parts;
       e.q = s->q;
       e.kc = kc;
       e.vc = vc;
@@ -785,12 +785,11 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.ssq = nullptr;
       e.gnext = W.g2;
       e.ld = d;
-      gemm_f32((const float*)W.wo, d, dm.Hq * D, (const float*)s->o, dm.Hq * D, M, e, st);
-      norm_rows_f32(s->x, M, d, nullptr, nullptr, s->ssq, st);
+      ssq_parts = gemm_f32((const float*)W.wo, d, dm.Hq * D, (const float*)s->o, dm.Hq * D, M, e, st);
       e = base;
       e.kind = EPI_SWIGLU;
       e.ssq = s->ssq;
-      e.ssq_parts = 1;
+      e.ssq_parts = ssq_parts;
       e.h = s->h;
       e.ld = dm.dff;
       gemm_f32((const float*)W.w13, 2 * dm.dff, d, (const float*)s->xn, d, M, e, st);
@@ -799,13 +798,12 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.ssq = nullptr;
       e.gnext = (l + 1 < dm.L) ? m->layers[l + 1].g1 : m->gf;
       e.ld = d;
-      gemm_f32((const float*)W.w2, d, dm.dff, (const float*)s->h, dm.dff, M, e, st);
-      norm_rows_f32(s->x, M, d, nullptr, nullptr, s->ssq, st);
+      ssq_parts = gemm_f32((const float*)W.w2, d, dm.dff, (const float*)s->h, dm.dff, M, e, st);
     }
     EpiArgs e = base;
     e.kind = EPI_LOGITS;
     e.ssq = s->ssq;
-    e.ssq_parts = 1;
+    e.ssq_parts = ssq_parts;
     e.logits = s->logits;
     e.ld = dm.Vimg;
     if (lm_mode == 0) {
@@ -858,7 +856,10 @@ void size_workspaces(const Dims& dm, const ssd_model* m, int B, int P, int Kmax,
   apart = 0;
   acnt = 0;
   ssq_parts_max = 1;
-  if (!dm.bf16) return;
+  if (!dm.bf16) {
+    ssq_parts_max = f32_feature_blocks(dm.d);
+    return;
+  }
   const int Nqkv = (dm.Hq + 2 * dm.Hkv) * dm.D;
   // every token-tile class a plan can fall in: up to 16, 32 and 64 tokens,
   // 65..128 (64-token tiles), beyond 128 (tiled, every row-tile count up to
@@ -1302,30 +1303,28 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
   base.h_plane = w.hb_plane;
   base.logits = w.logits;
   if (!dm.bf16) {
-    // fp32 models: plain fp32 GEMMs, one row sum of squares per norm
+    // fp32 models: plain fp32 GEMMs
     draft_input_f32(hin, (const float*)m->emb, tok, R, d, (float*)w.z, st);
     EpiArgs e = base;
     e.kind = EPI_RESID;  // u = W0 [h; e]; n = g * u
     e.gnext = h->g;
     e.ld = d;
-    gemm_f32((const float*)h->w0, d, 2 * d, (const float*)w.z, 2 * d, R, e, st);
-    norm_rows_f32(w.x, R, d, nullptr, nullptr, w.ssq, st);
+    int parts = gemm_f32((const float*)h->w0, d, 2 * d, (const float*)w.z, 2 * d, R, e, st);
     e = base;
     e.kind = EPI_SWIGLU;  // SwiGLU(n / rms(u))
     e.ssq = w.ssq;
-    e.ssq_parts = 1;
+    e.ssq_parts = parts;
     e.ld = mi;
     gemm_f32((const float*)h->w13, 2 * mi, d, (const float*)w.xn, d, R, e, st);
     e = base;
     e.kind = EPI_RESID;  // h_hat = u + W2 (...); n = g_f * h_hat
     e.gnext = m->gf;
     e.ld = d;
-    gemm_f32((const float*)h->w2, d, mi, (const float*)w.hb, mi, R, e, st);
-    norm_rows_f32(w.x, R, d, nullptr, nullptr, w.ssq, st);
+    parts = gemm_f32((const float*)h->w2, d, mi, (const float*)w.hb, mi, R, e, st);
     e = base;
     e.kind = EPI_LOGITS;
     e.ssq = w.ssq;
-    e.ssq_parts = 1;
+    e.ssq_parts = parts;
     e.ld = dm.Vimg;
     gemm_f32((const float*)m->wlm, dm.Vimg, d, (const float*)w.xn, d, R, e, st);
   } else {
@@ -1463,7 +1462,7 @@ ssd_status ssd_draft_head_init(ssd_model* m, int32_t mi, const void* weights, in
     }
     // workspaces for every plan a run of up to max_rows rows can meet
     size_t gpart = 0, gcnt = 0;
-    int parts = 1;
+    int parts = dm.bf16 ? 1 : f32_feature_blocks(d);
     for (int Mc : gemm_row_classes()) {
       if (!dm.bf16) break;
       for (auto nk : {std::make_pair(d, 2 * d), std::make_pair(2 * mi, d), std::make_pair(d, mi),
@@ -1553,7 +1552,7 @@ ssd_status ssd_draft_head_run_noalloc(ssd_draft_head* h, int32_t R, const float*
   const int d = h->d, mi = h->mi;
   // carve this call's workspace out of the static array: every region 256-byte aligned
   size_t gpart = 0, gcnt = 0;
-  int parts = 1;
+  int parts = dm.bf16 ? 1 : f32_feature_blocks(d);
   if (dm.bf16) {
     const std::pair<int, int> nk[4] = {{d, 2 * d}, {2 * mi, d}, {d, mi}, {dm.Vimg, d}};
     for (const auto& p : nk) {

@@ -207,7 +207,11 @@ size_t gemm_partials_floats(const GemmPlan& p, int M);
 // y = W x for split inputs in[M][K] (row stride ld_in, lo plane in_plane elements after hi); epilogue per `epi`.
 void gemm_bf16(const GemmPlan& p, const void* Wpacked, int N, int K, const void* in, size_t in_plane, int ld_in,
                int M, const EpiArgs& epi, float* partials, unsigned* counters, hipStream_t st);
-void gemm_f32(const float* W, int N, int K, const float* in, int ld_in, int M, const EpiArgs& epi, hipStream_t st);
+// fp32 projection; a residual epilogue leaves its per-token sums of x^2 in
+// epi.ssq_out and the call returns their part count (0 for other epilogues)
+int gemm_f32(const float* W, int N, int K, const float* in, int ld_in, int M, const EpiArgs& epi, hipStream_t st);
+// 16-feature blocks of an fp32 projection: the most parts a residual one writes
+inline int f32_feature_blocks(int N) { return (N + 15) / 16; }
 
 void pack_bf16_tiles(const uint16_t* src, const int* rowmap, int N, int K, void* dst, hipStream_t st);
 void gather_rows_f32(const float* src, const int* rowmap, int N, int K, float* dst, hipStream_t st);
@@ -215,8 +219,8 @@ void gather_rows_f32(const float* src, const int* rowmap, int N, int K, float* d
 // x[t] = E[tok[t]]; xn = g * x (split planes for bf16 models); ssq[t] = sum x^2 (one part)
 void embed(const Dims& dm, const void* emb, const int* tok, int M, const float* g, float* x, void* xn,
            size_t xn_plane, float* ssq, hipStream_t st);
-// fp32 path: xn = g * x, ssq[t] = sum x^2 (one part)
-void norm_rows_f32(const float* x, int M, int d, const float* g, float* xn, float* ssq, hipStream_t st);
+// fp32 path: ssq[t] = sum x^2 of row t (one part)
+void norm_rows_f32(const float* x, int M, int d, float* ssq, hipStream_t st);
 
 struct AttnKArgs {
   const uint16_t* q;   // [B][Hkv][qrows_pad x D tiles], hi plane then lo plane (q_plane elements apart)
