@@ -10,8 +10,8 @@
 //       round's logits as its next reference q (an accepted one keeps q).
 // q is the stored reference warped like p, or a point mass at t.
 // Probabilities, sums and the inverse CDF are float64; the top-k set is
-// found by an 8-bit radix select over order-preserving float keys, ties at
-// the boundary resolved towards lower codes.  Uniforms: 24-bit SplitMix64
+// found by a radix select (11, 11 and 10 bits) over order-preserving float
+// keys, ties at the boundary resolved towards lower codes.  Uniforms: 24-bit SplitMix64
 // outputs at a counter built from (sequence, position, round, stream)
 // (Steele, Lea & Flood, OOPSLA 2014).
 #include "ssd_internal.h"
@@ -108,56 +108,9 @@ __device__ __forceinline__ double uniform24(unsigned long long seed, int b, int 
 }
 
 struct SelShared {
-  double dred[NT_SEL / 64];
   float fred[NT_SEL / 64];
   int ired[NT_SEL / 64];
-  int hist[256];
-  int tie_base[NT_SEL];
-  double pre[NT_SEL];
-  int bc_i[4];
-  double bc_d[4];
-  unsigned bc_u[2];
 };
-
-__device__ double block_sum_d(double v, SelShared& sh) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh.dred[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = ((sh.dred[0] + sh.dred[1]) + sh.dred[2]) + sh.dred[3];
-  __syncthreads();
-  return r;
-}
-
-__device__ float block_max_f(float v, SelShared& sh) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh.fred[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = fmaxf(fmaxf(sh.fred[0], sh.fred[1]), fmaxf(sh.fred[2], sh.fred[3]));
-  __syncthreads();
-  return r;
-}
-
-__device__ int block_min_i(int v, SelShared& sh) {
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh.ired[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int r = min(min(sh.ired[0], sh.ired[1]), min(sh.ired[2], sh.ired[3]));
-  __syncthreads();
-  return r;
-}
-
-__device__ int block_max_i(int v, SelShared& sh) {
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh.ired[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int r = max(max(sh.ired[0], sh.ired[1]), max(sh.ired[2], sh.ired[3]));
-  __syncthreads();
-  return r;
-}
 
 // argmax with ties to the lowest index over row[0..V)
 // Lowest index among the maxima.  Thread t scans elements 4t + 1024 j .. +3
@@ -233,282 +186,479 @@ __device__ int block_argmax(const float* row, int V, SelShared& sh) {
   return ri;
 }
 
-// The kept set of top_k(row): keys above `thr`, plus the first `need` keys equal to
-// `thr` in index order.  `all` when no truncation applies.
-struct TopK {
-  uint32_t thr;
-  int need;
-  bool all;
+// ---------------- rules (B) and (C): warped distributions ----------------
+// One workgroup of 16 waves per position.  A row is read in 16-byte loads,
+// wave w walking the w-th contiguous segment, so every pass over it is
+// coalesced and index order is wave order, then lane order.  A kept set is
+// held as a threshold key and the index of its last boundary tie, a test any
+// thread can make for any code; where it has at most SMP_LIST codes it is
+// also compacted into LDS in index order, and the float64 exponentials (about
+// 50 instructions each) run over those codes instead of the whole row.
+// Four 32-token rows, 16384 codes, top 2000, rule C: 360 -> 50 us a launch (59
+// with every pass reading the row again); two 24-token rows, rule B: 151 -> 25.
+constexpr int SMP_T = 1024, SMP_W = SMP_T / 64;
+constexpr int SMP_LIST = 4096;
+constexpr int SMP_HELD = 256 * SMP_W;  // codes a workgroup holds in registers per group of a wave
+constexpr int SMP_BINS = 2048;
+
+struct SmpShared {
+  int hist[SMP_BINS];
+  int idx[SMP_LIST];   // kept codes in index order, and their logits
+  float val[SMP_LIST];
+  double dred[SMP_W];
+  int ired[2][SMP_W];
+  float fred[SMP_W];
+  unsigned bc[4];
 };
 
-struct KeepIter {
-  uint32_t thr;
-  int need, rank;
-  bool all;
-  __device__ __forceinline__ bool next(uint32_t key) {
-    if (all || key > thr) return true;
-    if (key == thr) {
-      bool k = rank < need;
-      ++rank;
-      return k;
-    }
-    return false;
-  }
+// row elements v .. v + 3 (V a multiple of four and the row 16-byte aligned: one load); n of them exist
+struct Quad {
+  float x[4];
+  int n;
 };
-
-__device__ TopK topk_select(const float* row, int V, int top_k, SelShared& sh, int* tie_base_out) {
-  TopK tk;
-  tk.all = (top_k <= 0 || top_k >= V);
-  tk.thr = 0;
-  tk.need = 0;
-  const int VPT = (V + NT_SEL - 1) / NT_SEL;
-  const int lo = threadIdx.x * VPT, hi = min(lo + VPT, V);
-  if (tk.all) {
-    *tie_base_out = 0;
-    return tk;
-  }
-  uint32_t prefix = 0, mask = 0;
-  int remaining = top_k;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    sh.hist[threadIdx.x] = 0;
-    __syncthreads();
-    for (int v = lo; v < hi; ++v) {
-      uint32_t key = fkey(row[v]);
-      if ((key & mask) == prefix) atomicAdd(&sh.hist[(key >> shift) & 255u], 1);
+__device__ __forceinline__ Quad load_quad(const float* row, int v, int V, bool vec) {
+  Quad q;
+  q.n = max(0, min(4, V - v));
+  if (vec) {
+    if (q.n > 0) {
+      const float4 f = *(const float4*)(row + v);
+      q.x[0] = f.x, q.x[1] = f.y, q.x[2] = f.z, q.x[3] = f.w;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int cum = 0, dgt = 255;
-      for (; dgt > 0; --dgt) {
-        if (cum + sh.hist[dgt] >= remaining) break;
-        cum += sh.hist[dgt];
-      }
-      sh.bc_i[0] = dgt;
-      sh.bc_i[1] = remaining - cum;
-    }
-    __syncthreads();
-    prefix |= (uint32_t)sh.bc_i[0] << shift;
-    mask |= 0xFFu << shift;
-    remaining = sh.bc_i[1];
-    __syncthreads();
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < q.n) q.x[e] = row[v + e];
   }
-  tk.thr = prefix;
-  tk.need = remaining;
-  // exclusive prefix of ties per thread, in index order
-  int nt = 0;
-  for (int v = lo; v < hi; ++v) nt += (fkey(row[v]) == prefix);
-  sh.tie_base[threadIdx.x] = nt;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int i = 0; i < NT_SEL; ++i) {
-      int c = sh.tie_base[i];
-      sh.tie_base[i] = acc;
-      acc += c;
-    }
-  }
-  __syncthreads();
-  *tie_base_out = sh.tie_base[threadIdx.x];
-  __syncthreads();
-  return tk;
+  return q;
 }
 
-// A warped distribution p_v = [v kept] exp(z_v - mz) / Z, z = row / T.
-struct Warp {
+// The segment of this wave, in groups of 256 codes (four per lane).  NG > 0:
+// read once and held in registers (rows of up to 4096 NG codes: the kept set
+// takes five passes over them); NG = 0: read again by every pass.
+template <int NG>
+struct Seg {
   const float* row;
-  TopK tk;
-  int tie_base;
-  double T, mz, Z;
-  __device__ __forceinline__ KeepIter iter() const { return KeepIter{tk.thr, tk.need, tie_base, tk.all}; }
+  int beg, groups, V;
+  bool vec;
+  Quad held[NG > 0 ? NG : 1];
+  __device__ __forceinline__ Seg(const float* r, int v) : row(r), V(v) {
+    const int all = (V + 255) / 256, per = (all + SMP_W - 1) / SMP_W, w = threadIdx.x >> 6;
+    beg = w * per * 256;
+    groups = max(0, min(per, all - w * per));
+    vec = (V & 3) == 0 && (((uintptr_t)row) & 15) == 0;
+    if constexpr (NG > 0) {
+#pragma unroll
+      for (int i = 0; i < NG; ++i) {
+        held[i] = Quad{};
+        if (i < groups) held[i] = load_quad(row, code(i), V, vec);
+      }
+    }
+  }
+  // first of this lane's four codes in group i
+  __device__ __forceinline__ int code(int i) const { return beg + i * 256 + (threadIdx.x & 63) * 4; }
+  // fn(first code, quad) over the groups in order (every lane of the wave together)
+  template <int U = 4, typename F>
+  __device__ __forceinline__ void each(F fn) const {
+    if constexpr (NG > 0) {
+#pragma unroll
+      for (int i = 0; i < NG; ++i)
+        if (i < groups) fn(code(i), held[i]);
+    } else {
+#pragma unroll U
+      for (int i = 0; i < groups; ++i) fn(code(i), load_quad(row, code(i), V, vec));
+    }
+  }
 };
 
-__device__ Warp make_warp(const float* row, int V, int top_k, double T, SelShared& sh) {
-  Warp w;
-  w.row = row;
-  int tb;
-  w.tk = topk_select(row, V, top_k, sh, &tb);
-  w.tie_base = tb;
-  w.T = T;
-  const int VPT = (V + NT_SEL - 1) / NT_SEL;
-  const int lo = threadIdx.x * VPT, hi = min(lo + VPT, V);
-  float mx = -INFINITY;
-  for (int v = lo; v < hi; ++v) mx = fmaxf(mx, row[v]);
-  mx = block_max_f(mx, sh);
-  w.mz = (double)mx / T;
-  double s = 0.0;
-  KeepIter it = w.iter();
-  for (int v = lo; v < hi; ++v) {
-    float x = row[v];
-    if (it.next(fkey(x))) s += exp((double)x / T - w.mz);
-  }
-  w.Z = block_sum_d(s, sh);
-  return w;
-}
-
-// probability of one code under a warp (every thread returns the same value)
-__device__ double warp_prob(const Warp& w, int t, int V, SelShared& sh) {
-  const int VPT = (V + NT_SEL - 1) / NT_SEL;
-  const int lo = threadIdx.x * VPT, hi = min(lo + VPT, V);
-  if (t >= lo && t < hi) {
-    KeepIter it = w.iter();
-    double pv = 0.0;
-    for (int v = lo; v <= t; ++v) {
-      float x = w.row[v];
-      bool k = it.next(fkey(x));
-      if (v == t) pv = k ? exp((double)x / w.T - w.mz) / w.Z : 0.0;
-    }
-    sh.bc_d[0] = pv;
-  }
+__device__ double smp_sum(double v, SmpShared& sh) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   __syncthreads();
-  double r = sh.bc_d[0];
+  if ((threadIdx.x & 63) == 0) sh.dred[threadIdx.x >> 6] = v;
   __syncthreads();
+  double r = 0.0;
+#pragma unroll
+  for (int w = 0; w < SMP_W; ++w) r += sh.dred[w];
   return r;
 }
 
-// inverse CDF over per-code weights produced by `wf(v, x_p, keep_p, x_q, keep_q)`;
-// smallest v with cumsum > u * total; fallback: last code of positive weight.
-template <typename WF>
-__device__ int block_invcdf(int V, double u, WF wf, SelShared& sh) {
-  const int VPT = (V + NT_SEL - 1) / NT_SEL;
-  const int lo = threadIdx.x * VPT, hi = min(lo + VPT, V);
-  double s = 0.0;
-  int lastpos = -1;
-  wf.begin();
-  for (int v = lo; v < hi; ++v) {
-    double w = wf(v);
-    s += w;
-    if (w > 0.0) lastpos = v;
+// A warped distribution p_v = [v kept] exp(z_v - mz) / Z, z = row / T.
+struct Dist {
+  const float* row;
+  double T, mz, Z;
+  uint32_t thr;  // kept: keys above thr, and keys equal to it up to index cut
+  int cut;
+  bool all;
+  int n;         // kept codes listed in LDS (-1: not listed)
+  __device__ __forceinline__ bool keep(uint32_t key, int v) const {
+    return all || key > thr || (key == thr && v <= cut);
   }
-  sh.pre[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double acc = 0.0;
-    for (int i = 0; i < NT_SEL; ++i) {
-      double c = sh.pre[i];
-      sh.pre[i] = acc;
-      acc += c;
+  __device__ __forceinline__ double prob(float x) const { return exp((double)x / T - mz) / Z; }
+  // probability of any code
+  __device__ __forceinline__ double at(int v) const {
+    const float x = row[v];
+    return keep(fkey(x), v) ? prob(x) : 0.0;
+  }
+};
+
+// Kept set and normaliser of top_k(row / T).  Every thread returns the same
+// Dist; the LDS list belongs to the last call.
+template <int NG>
+__device__ Dist make_dist(const float* row, int V, int top_k, double T, SmpShared& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const Seg<NG> sg(row, V);
+  Dist d;
+  d.row = row;
+  d.T = T;
+  d.all = top_k <= 0 || top_k >= V;
+  d.thr = 0;
+  d.cut = V;
+  d.n = -1;
+  d.Z = 1.0;
+  float mx = -INFINITY;
+  int need = 0;
+  if (d.all) {
+    sg.each([&](int, const Quad& q) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < q.n) mx = fmaxf(mx, q.x[e]);
+    });
+  } else {
+    uint32_t prefix = 0, mask = 0;
+    int remaining = top_k;
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {
+      const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+      const uint32_t dm = pass == 2 ? 1023u : 2047u;
+      __syncthreads();  // the previous user of the shared arrays is done
+      sh.hist[tid] = 0;
+      sh.hist[tid + SMP_T] = 0;
+      __syncthreads();
+      sg.each([&](int, const Quad& q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e < q.n) {
+            const uint32_t key = fkey(q.x[e]);
+            if (pass == 0) mx = fmaxf(mx, q.x[e]);
+            if ((key & mask) == prefix) atomicAdd(&sh.hist[(key >> shift) & dm], 1);
+          }
+      });
+      __syncthreads();
+      // digits in descending order, two per thread: the one whose running
+      // count first reaches `remaining`
+      const int b0 = SMP_BINS - 1 - 2 * tid;
+      const int h0 = sh.hist[b0], h1 = sh.hist[b0 - 1];
+      int inc = h0 + h1;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o);
+        if (lane >= o) inc += t;
+      }
+      if (lane == 63) sh.ired[0][wave] = inc;
+      __syncthreads();
+      int before = 0;
+#pragma unroll
+      for (int w = 0; w < SMP_W; ++w) before += w < wave ? sh.ired[0][w] : 0;
+      inc += before;
+      const int exc = inc - h0 - h1;
+      if (exc < remaining && inc >= remaining) {  // one thread
+        const bool second = exc + h0 < remaining;
+        sh.bc[0] = second ? b0 - 1 : b0;
+        sh.bc[1] = remaining - (second ? exc + h0 : exc);
+        sh.bc[2] = second ? h1 : h0;
+      }
+      __syncthreads();
+      prefix |= sh.bc[0] << shift;
+      mask |= dm << shift;
+      remaining = (int)sh.bc[1];
     }
-    sh.bc_d[1] = acc;
-  }
-  __syncthreads();
-  const double total = sh.bc_d[1];
-  const double target = u * total;
-  double c = sh.pre[threadIdx.x];
-  int cand = 0x7fffffff;
-  wf.begin();
-  for (int v = lo; v < hi; ++v) {
-    c += wf(v);
-    if (c > target) {
-      cand = v;
-      break;
+    d.thr = prefix;
+    need = remaining;                        // keys equal to thr that are kept
+    const int ties = (int)sh.bc[2];          // of this many
+    const bool list = top_k <= SMP_LIST;
+    if (list || ties != need) {
+      // keys above and equal to thr per wave; then the kept codes' places in index order
+      int gt = 0, eq = 0;
+      sg.each([&](int, const Quad& q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e < q.n) {
+            const uint32_t key = fkey(q.x[e]);
+            gt += key > d.thr;
+            eq += key == d.thr;
+          }
+      });
+      for (int o = 32; o > 0; o >>= 1) {
+        gt += __shfl_xor(gt, o);
+        eq += __shfl_xor(eq, o);
+      }
+      if (lane == 0) {
+        sh.ired[0][wave] = gt;
+        sh.ired[1][wave] = eq;
+      }
+      __syncthreads();
+      int gtb = 0, eqb = 0;
+#pragma unroll
+      for (int w = 0; w < SMP_W; ++w) {
+        gtb += w < wave ? sh.ired[0][w] : 0;
+        eqb += w < wave ? sh.ired[1][w] : 0;
+      }
+      int at = gtb + min(eqb, need);  // place of this wave's next kept code
+      const uint64_t below = (1ull << lane) - 1;
+      sg.each([&](int v, const Quad& q) {
+        bool kg[4], ke[4];
+        int eq_below = eqb, eq_all = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t key = e < q.n ? fkey(q.x[e]) : 0u;
+          kg[e] = e < q.n && key > d.thr;
+          ke[e] = e < q.n && key == d.thr;
+          const uint64_t m = __ballot(ke[e]);
+          eq_below += __popcll(m & below);
+          eq_all += __popcll(m);
+        }
+        int k_below = at, k_all = 0;
+        bool kept[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          kept[e] = kg[e] || (ke[e] && eq_below < need);
+          if (ke[e] && eq_below == need - 1) sh.bc[3] = (unsigned)(v + e);  // the last kept tie: one lane
+          eq_below += ke[e];
+          const uint64_t m = __ballot(kept[e]);
+          k_below += __popcll(m & below);
+          k_all += __popcll(m);
+        }
+        if (list) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (kept[e]) {
+              sh.idx[k_below] = v + e;
+              sh.val[k_below] = q.x[e];
+              ++k_below;
+            }
+        }
+        at += k_all;
+        eqb += eq_all;
+      });
+      __syncthreads();
+      d.cut = (int)sh.bc[3];
+      if (list) d.n = top_k;
     }
   }
+  // largest logit, then the normaliser over the kept codes
+  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  if (lane == 0) sh.fred[wave] = mx;
   __syncthreads();
-  int best = block_min_i(cand, sh);
-  if (best == 0x7fffffff) best = block_max_i(lastpos, sh);
-  return best;
+#pragma unroll
+  for (int w = 0; w < SMP_W; ++w) mx = fmaxf(mx, sh.fred[w]);
+  d.mz = (double)mx / T;
+  double z = 0.0;
+  if (d.n >= 0) {
+    for (int i = tid; i < d.n; i += SMP_T) z += exp((double)sh.val[i] / T - d.mz);
+  } else {
+    Seg<0>(row, V).template each<1>([&](int v, const Quad& q) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < q.n && d.keep(fkey(q.x[e]), v + e)) z += exp((double)q.x[e] / T - d.mz);
+    });
+  }
+  d.Z = smp_sum(z, sh);
+  return d;
 }
 
-// weights of p (normalised)
-struct PW {
-  const Warp* p;
-  KeepIter ip;
-  __device__ void begin() { ip = p->iter(); }
-  __device__ double operator()(int v) {
-    float x = p->row[v];
-    return ip.next(fkey(x)) ? exp((double)x / p->T - p->mz) / p->Z : 0.0;
-  }
-};
-
-// residual [p - q]_+ with q a warp or a point mass at `pt`
-struct RW {
-  const Warp* p;
-  const Warp* q;  // nullptr -> point mass
-  int pt;
-  KeepIter ip, iq;
-  __device__ void begin() {
-    ip = p->iter();
-    if (q) iq = q->iter();
-  }
-  __device__ double operator()(int v) {
-    float x = p->row[v];
-    double pv = ip.next(fkey(x)) ? exp((double)x / p->T - p->mz) / p->Z : 0.0;
-    double qv;
-    if (q) {
-      float y = q->row[v];
-      qv = iq.next(fkey(y)) ? exp((double)y / q->T - q->mz) / q->Z : 0.0;
-    } else {
-      qv = (v == pt) ? 1.0 : 0.0;
+// Inverse CDF over the kept codes of p (whose list, if any, is in LDS) with
+// weights wf(v, p_v): the smallest code whose running sum exceeds u * total,
+// else the last code of positive weight.  *total: the sum of the weights.
+template <typename WF>
+__device__ int smp_invcdf(const Dist& p, int V, double u, WF wf, double* total, SmpShared& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool list = p.n >= 0;
+  // this thread's weights in index order: four consecutive list entries, or
+  // (a wave's codes) the sum of its segment
+  constexpr int EPT = SMP_LIST / SMP_T;
+  double w[EPT], s = 0.0;
+  int last = -1;
+  if (list) {
+    const int per = (p.n + SMP_T - 1) / SMP_T;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int i = tid * per + e;
+      w[e] = 0.0;
+      if (e < per && i < p.n) {
+        w[e] = wf(sh.idx[i], p.prob(sh.val[i]));
+        s += w[e];
+        if (w[e] > 0.0) last = sh.idx[i];
+      }
     }
-    double r = pv - qv;
-    return r > 0.0 ? r : 0.0;
+  } else {
+    Seg<0>(p.row, V).each<1>([&](int v, const Quad& q) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < q.n && p.keep(fkey(q.x[e]), v + e)) {
+          const double x = wf(v + e, p.prob(q.x[e]));
+          s += x;
+          if (x > 0.0) last = v + e;
+        }
+    });
   }
-};
+  // running sums: over the lanes of a wave (list order), then over the waves
+  double inc = s;
+  for (int o = 1; o < 64; o <<= 1) {
+    const double t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  __syncthreads();
+  if (lane == 63) sh.dred[wave] = inc;
+  __syncthreads();
+  double base = 0.0, tot = 0.0;
+#pragma unroll
+  for (int x = 0; x < SMP_W; ++x) {
+    if (x == wave) base = tot;
+    tot += sh.dred[x];
+  }
+  *total = tot;
+  const double target = u * tot;
+  int cand = 0x7fffffff;
+  if (list) {
+    const int per = (p.n + SMP_T - 1) / SMP_T;
+    double c = base + (inc - s);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int i = tid * per + e;
+      c += w[e];
+      if (e < per && i < p.n && c > target && cand == 0x7fffffff) cand = sh.idx[i];
+    }
+  } else if (base + sh.dred[wave] > target) {
+    // the wave walks its segment in index order until the sum passes the target
+    double run = base;
+    bool found = false;
+    Seg<0>(p.row, V).each<1>([&](int v, const Quad& q) {
+      if (found) return;
+      double x[4], t = 0.0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] = e < q.n && p.keep(fkey(q.x[e]), v + e) ? wf(v + e, p.prob(q.x[e])) : 0.0;
+        t += x[e];
+      }
+      double ti = t;
+      for (int o = 1; o < 64; o <<= 1) {
+        const double y = __shfl_up(ti, o);
+        if (lane >= o) ti += y;
+      }
+      double c = run + (ti - t);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        c += x[e];
+        if (e < q.n && c > target && cand == 0x7fffffff) cand = v + e;
+      }
+      run += __shfl(ti, 63);
+      found = __ballot(cand != 0x7fffffff) != 0;
+    });
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    cand = min(cand, __shfl_xor(cand, o));
+    last = max(last, __shfl_xor(last, o));
+  }
+  if (lane == 0) {
+    sh.ired[0][wave] = cand;
+    sh.ired[1][wave] = last;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < SMP_W; ++x) {
+    cand = min(cand, sh.ired[0][x]);
+    last = max(last, sh.ired[1][x]);
+  }
+  return cand != 0x7fffffff ? cand : last;
+}
 
-__global__ __launch_bounds__(NT_SEL) void select_kernel(SelectArgs a) {
+// position k of sequence b is already chosen (a fixed first position or an end-of-line token)
+__device__ __forceinline__ bool sel_fixed(const SelectArgs& a, int b, int k) {
+  return k < a.n_fixed || (a.eol_period > 0 && (a.f[b] + k - a.eol_base) % a.eol_period == a.eol_period - 1);
+}
+
+// scoring logits of position k of sequence b: the output at k - 1, the carry for k = 0
+__device__ __forceinline__ const float* sel_logits(const SelectArgs& a, int b, int k) {
+  return k == 0 ? a.carry + (size_t)b * a.Vimg : a.logits + ((size_t)b * a.K + k - 1) * a.Vimg;
+}
+
+// rule (A), and the strict mode's argmax
+__global__ __launch_bounds__(NT_SEL) void select_greedy_kernel(SelectArgs a) {
   __shared__ SelShared sh;
   const int k = blockIdx.x, b = blockIdx.y;
   const int V = a.Vimg;
   const size_t idx = (size_t)b * a.K + k;
-  if (k < a.n_fixed ||
-      (a.eol_period > 0 && (a.f[b] + k - a.eol_base) % a.eol_period == a.eol_period - 1)) {
-    if (threadIdx.x == 0) a.accept[idx] = 0;  // fixed: already chosen, or an end-of-line token
+  if (sel_fixed(a, b, k)) {
+    if (threadIdx.x == 0) a.accept[idx] = 0;
     return;
   }
-  const float* L = (k == 0) ? a.carry + (size_t)b * V : a.logits + (idx - 1) * V;
+  int t = a.tokens[idx] - a.img_lo;
+  t = t < 0 ? 0 : (t >= V ? V - 1 : t);
+  const int newt = block_argmax(sel_logits(a, b, k), V, sh);
+  if (threadIdx.x == 0) {
+    if (a.truncate) a.amax[idx] = newt;
+    a.tokens[idx] = newt + a.img_lo;
+    a.accept[idx] = newt == t ? 1 : 0;
+    if (newt == t) atomicAdd(&a.count[b], 1);
+  }
+}
+
+// rules (B) and (C)
+template <int NG>
+__global__ __launch_bounds__(SMP_T) void select_sample_kernel(SelectArgs a) {
+  __shared__ SmpShared sh;
+  const int k = blockIdx.x, b = blockIdx.y;
+  const int V = a.Vimg;
+  const size_t idx = (size_t)b * a.K + k;
+  if (sel_fixed(a, b, k)) {
+    if (threadIdx.x == 0) a.accept[idx] = 0;
+    return;
+  }
+  const float* L = sel_logits(a, b, k);
   int t = a.tokens[idx] - a.img_lo;
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
   const int pos = a.f[b] + k;
+  const double u1 = uniform24(a.seed, b, pos, a.round, 1);
   int newt = t;
   bool acc = false;
-  if (a.rule == SSD_GREEDY || a.truncate) {
-    newt = block_argmax(L, V, sh);
-    acc = (newt == t);
-    if (a.truncate && threadIdx.x == 0) a.amax[idx] = newt;
+  double tot;
+  if (a.rule == SSD_SAMPLE) {
+    const Dist p = make_dist<NG>(L, V, a.top_k, a.temperature, sh);
+    newt = smp_invcdf(p, V, u1, [](int, double pv) { return pv; }, &tot, sh);
+    acc = newt == t;
   } else {
-    Warp p = make_warp(L, V, a.top_k, a.temperature, sh);
-    if (a.rule == SSD_SAMPLE) {
-      const double u1 = uniform24(a.seed, b, pos, a.round, 1);
-      PW wf{&p, KeepIter{}};
-      newt = block_invcdf(V, u1, wf, sh);
-      acc = (newt == t);
+    const int slot = pos % a.ring;
+    const bool has_ref = a.ref_flag[(size_t)b * a.ring + slot] != 0;
+    float* refrow = a.ref + ((size_t)b * a.ring + slot) * V;
+    Dist q{};
+    double qt = 1.0;  // a point mass at t without a reference
+    if (has_ref) {
+      q = make_dist<NG>(refrow, V, a.top_k, a.temperature, sh);
+      qt = q.at(t);
+    }
+    const Dist p = make_dist<NG>(L, V, a.top_k, a.temperature, sh);
+    const double pt = p.at(t);
+    const double alpha = qt > 0.0 ? fmin(pt / qt, 1.0) : (pt > 0.0 ? 1.0 : 0.0);
+    const double u0 = uniform24(a.seed, b, pos, a.round, 0);
+    if (u0 < alpha) {
+      acc = true;
     } else {
-      const int slot = pos % a.ring;
-      const bool has_ref = a.ref_flag[(size_t)b * a.ring + slot] != 0;
-      float* refrow = a.ref + ((size_t)b * a.ring + slot) * V;
-      Warp q;
-      double qt = 1.0;
-      if (has_ref) {
-        q = make_warp(refrow, V, a.top_k, a.temperature, sh);
-        qt = warp_prob(q, t, V, sh);
-      }
-      const double pt = warp_prob(p, t, V, sh);
-      const double alpha = qt > 0.0 ? fmin(pt / qt, 1.0) : (pt > 0.0 ? 1.0 : 0.0);
-      const double u0 = uniform24(a.seed, b, pos, a.round, 0);
-      if (u0 < alpha) {
-        acc = true;
+      // residual [p - q]_+, positive only where p keeps a code
+      const int r = smp_invcdf(
+          p, V, u1,
+          [&](int v, double pv) {
+            const double x = pv - (has_ref ? q.at(v) : (v == t ? 1.0 : 0.0));
+            return x > 0.0 ? x : 0.0;
+          },
+          &tot, sh);
+      if (!(tot > 0.0)) {
+        acc = true;  // zero residual mass (rounding only): keep the token
       } else {
-        RW wf{&p, has_ref ? &q : nullptr, t, KeepIter{}, KeepIter{}};
-        // total residual mass (same association as the inverse CDF's)
-        const double u1 = uniform24(a.seed, b, pos, a.round, 1);
-        // zero residual (rounding only): keep the token
-        double s = 0.0;
-        {
-          const int VPT = (V + NT_SEL - 1) / NT_SEL;
-          const int lo = threadIdx.x * VPT, hi = min(lo + VPT, V);
-          wf.begin();
-          for (int v = lo; v < hi; ++v) s += wf(v);
-        }
-        const double tot = block_sum_d(s, sh);
-        if (!(tot > 0.0)) {
-          acc = true;
-        } else {
-          newt = block_invcdf(V, u1, wf, sh);
-          acc = false;
-          // the rejected position's reference becomes this round's backbone logits
-          for (int v = threadIdx.x; v < V; v += NT_SEL) refrow[v] = L[v];
-          if (threadIdx.x == 0) a.ref_flag[(size_t)b * a.ring + slot] = 1;
-        }
+        newt = r;
+        // the rejected position's reference becomes this round's backbone logits (every read of it is done)
+        if ((V & 3) == 0)
+          for (int v = threadIdx.x * 4; v < V; v += SMP_T * 4) *(float4*)(refrow + v) = *(const float4*)(L + v);
+        else
+          for (int v = threadIdx.x; v < V; v += SMP_T) refrow[v] = L[v];
+        if (threadIdx.x == 0) a.ref_flag[(size_t)b * a.ring + slot] = 1;
       }
     }
   }
@@ -520,7 +670,14 @@ __global__ __launch_bounds__(NT_SEL) void select_kernel(SelectArgs a) {
 }
 
 void select_tokens(const SelectArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(select_kernel, dim3(a.K, a.B), dim3(NT_SEL), 0, st, a);
+  if (a.rule == SSD_GREEDY || a.truncate)
+    hipLaunchKernelGGL(select_greedy_kernel, dim3(a.K, a.B), dim3(NT_SEL), 0, st, a);
+  else if (a.Vimg <= 4 * SMP_HELD)
+    hipLaunchKernelGGL(select_sample_kernel<4>, dim3(a.K, a.B), dim3(SMP_T), 0, st, a);
+  else if (a.Vimg <= 8 * SMP_HELD)
+    hipLaunchKernelGGL(select_sample_kernel<8>, dim3(a.K, a.B), dim3(SMP_T), 0, st, a);
+  else
+    hipLaunchKernelGGL(select_sample_kernel<0>, dim3(a.K, a.B), dim3(SMP_T), 0, st, a);
 }
 
 // truncate mode: accepted run, new frontier and carry
@@ -667,21 +824,22 @@ void set_ref_rows(int B, int K, int rows_per_b, int Vimg, const float* src, cons
 }
 
 // first image token from the carry: argmax (rule A) or a sample of the warped carry (uniform stream 2, round 0)
-__global__ __launch_bounds__(NT_SEL) void first_token_kernel(int Vimg, int img_lo, const float* carry, int rule, int top_k,
-                                                              double T, unsigned long long seed, const int* f,
-                                                              int* out_abs, int out_stride) {
+__global__ __launch_bounds__(NT_SEL) void first_argmax_kernel(int Vimg, int img_lo, const float* carry, int* out_abs,
+                                                              int out_stride) {
   __shared__ SelShared sh;
   const int b = blockIdx.x;
-  const float* L = carry + (size_t)b * Vimg;
-  int v;
-  if (rule == SSD_GREEDY) {
-    v = block_argmax(L, Vimg, sh);
-  } else {
-    Warp p = make_warp(L, Vimg, top_k, T, sh);
-    const double u1 = uniform24(seed, b, f[b], 0u, 2);
-    PW wf{&p, KeepIter{}};
-    v = block_invcdf(Vimg, u1, wf, sh);
-  }
+  const int v = block_argmax(carry + (size_t)b * Vimg, Vimg, sh);
+  if (threadIdx.x == 0) out_abs[(size_t)b * out_stride] = v + img_lo;
+}
+
+__global__ __launch_bounds__(SMP_T) void first_sample_kernel(int Vimg, int img_lo, const float* carry, int top_k,
+                                                             double T, unsigned long long seed, const int* f,
+                                                             int* out_abs, int out_stride) {
+  __shared__ SmpShared sh;
+  const int b = blockIdx.x;
+  const Dist p = make_dist<0>(carry + (size_t)b * Vimg, Vimg, top_k, T, sh);
+  double tot;
+  const int v = smp_invcdf(p, Vimg, uniform24(seed, b, f[b], 0u, 2), [](int, double pv) { return pv; }, &tot, sh);
   if (threadIdx.x == 0) out_abs[(size_t)b * out_stride] = v + img_lo;
 }
 
@@ -728,8 +886,11 @@ void draft_input_f32(const float* h, const float* emb, const int* tok, int R, in
 
 void first_token(int B, int Vimg, int img_lo, const float* carry, int rule, int top_k, double temperature,
                  unsigned long long seed, const int* f, int* out_abs, int out_stride, hipStream_t st) {
-  hipLaunchKernelGGL(first_token_kernel, dim3(B), dim3(NT_SEL), 0, st, Vimg, img_lo, carry, rule, top_k, temperature,
-                     seed, f, out_abs, out_stride);
+  if (rule == SSD_GREEDY)
+    hipLaunchKernelGGL(first_argmax_kernel, dim3(B), dim3(NT_SEL), 0, st, Vimg, img_lo, carry, out_abs, out_stride);
+  else
+    hipLaunchKernelGGL(first_sample_kernel, dim3(B), dim3(SMP_T), 0, st, Vimg, img_lo, carry, top_k, temperature, seed,
+                       f, out_abs, out_stride);
 }
 
 // The greedy argmax a of a logits row (lowest code among equal maxima) placed
