@@ -793,6 +793,24 @@ void xcc_probe(int* out, int n_wg, hipStream_t st) {
   hipLaunchKernelGGL(xcc_probe_kernel, dim3(n_wg), dim3(64), 0, st, out);
 }
 
+// Rotary table of a session: angles and their cosine and sine in float64,
+// rounded to fp32.  One thread per pair on the device: a session of 4352
+// positions and 64 pairs takes 6.7 us, against 8.4 ms for the same loop on
+// the host (278528 pow, cos and sin calls) plus the copy and its wait.
+__global__ __launch_bounds__(256) void rope_table_kernel(float2* tab, int positions, int half, double theta) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (size_t)positions * half) return;
+  const int p = (int)(i / half), j = (int)(i - (size_t)p * half);
+  const double ang = (double)p * pow(theta, -(double)j / half);
+  tab[i] = make_float2((float)cos(ang), (float)sin(ang));
+}
+
+void rope_table(float2* tab, int positions, int half, double theta, hipStream_t st) {
+  const size_t n = (size_t)positions * half;
+  hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, tab, positions, half,
+                     theta);
+}
+
 __global__ void fill_u32_kernel(unsigned* p, size_t n, unsigned v) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;

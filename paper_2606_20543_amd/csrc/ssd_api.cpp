@@ -1010,16 +1010,7 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
     fill_u32(s->gcnt, gcnt, 0u, st);
     fill_u32(s->acnt, acnt, 0u, st);
     fill_u32((unsigned*)s->d_f, B, 0u, st);
-    // rotary table (host double precision, rounded to fp32)
-    std::vector<float2> rope((size_t)s->Lmax * (dm.D / 2));
-    for (int p = 0; p < s->Lmax; ++p)
-      for (int j = 0; j < dm.D / 2; ++j) {
-        double inv = std::pow((double)dm.theta, -2.0 * j / dm.D);
-        double ang = (double)p * inv;
-        rope[(size_t)p * (dm.D / 2) + j] = make_float2((float)std::cos(ang), (float)std::sin(ang));
-      }
-    HIPCHK(hipMemcpyAsync(s->rope, rope.data(), rope.size() * sizeof(float2), hipMemcpyHostToDevice, st));
-    HIPCHK(hipStreamSynchronize(st));
+    rope_table(s->rope, s->Lmax, dm.D / 2, (double)dm.theta, st);
     HIPCHK(hipGetLastError());
   } catch (HipError& e) {
     delete s;

@@ -371,6 +371,8 @@ void place_argmax(const PlaceArgs& a, int B, hipStream_t st);
 void gather_block(const int* img, int img_stride, const int* f, int P, int K, int B, int* tok, hipStream_t st);
 // p[i] += delta
 void add_i32(int* p, int n, int delta, hipStream_t st);
+// rotary factors (cos, sin) of position p and pair j at tab[p * half + j]
+void rope_table(float2* tab, int positions, int half, double theta, hipStream_t st);
 // fill helpers (graph-capture safe)
 void fill_u32(unsigned* p, size_t n, unsigned v, hipStream_t st);
 // out[w] = XCD index workgroup w ran on
