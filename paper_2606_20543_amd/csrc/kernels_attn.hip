@@ -104,6 +104,17 @@ AttnPlan attn_plan(const Dims& dm, int B, int K, int max_ctx_now, int xcd, int g
   return p;
 }
 
+AttnPlan attn_plan_bound(const Dims& dm, int B, int K, int max_ctx) {
+  AttnPlan p = attn_plan(dm, B, K, max_ctx, 0);
+  const long units = (long)B * dm.Hkv * p.nqg, slots = p.qs ? 512 : 256;
+  const int steps = (std::max(max_ctx, 1) + AT_STEP - 1) / AT_STEP;  // chunks are whole steps
+  // few query groups: at most as many chunks as fit the slots; many: chunks of
+  // doubled length until all of them number 1024 or a chunk has 16 steps
+  const long n = units < slots ? slots / units : std::max(1024 / units, (long)(steps + 15) / 16);
+  p.nchunk = (int)std::max(1l, std::min({n, (long)AT_MAX_CHUNKS, (long)steps}));
+  return p;
+}
+
 size_t attn_partials_floats(const Dims& dm, const AttnPlan& p, int B) {
   return (size_t)B * dm.Hkv * p.nqg * p.nchunk * p.group_rows() * (dm.D + 2);
 }

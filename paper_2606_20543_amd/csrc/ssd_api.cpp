@@ -2,6 +2,7 @@
 // step and the image schedule driver.  See include/ssd.h for the contract.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -9,6 +10,7 @@
 #include <chrono>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -59,6 +61,112 @@ bool is_device_ptr(const void* p) {
   return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
 }
 
+// One device block kept by a model between its sessions: the workspace of the
+// session freed last, which the next session of about the same size takes over
+// (mapping and unmapping gigabytes costs milliseconds: 8 sequences of 4352
+// positions on a two-layer 8B model, 1.3 GB, 0.3 ms to allocate and 3.4 ms
+// to free).  Bounded by max_bytes, freed with the model, and released when any
+// allocation of the library runs out of memory.  A block comes in only after
+// its session's stream has drained.  Held jointly with the sessions, so a
+// session freed after its model still finds it (closed).
+class BlockPool {
+ public:
+  static std::shared_ptr<BlockPool> make() {
+    auto p = std::make_shared<BlockPool>();
+    std::lock_guard<std::mutex> lk(registry_mu());
+    registry().push_back(p);
+    return p;
+  }
+  ~BlockPool() { release(); }
+  // a block of at least `bytes` (and not more than twice as many), or nullptr
+  void* take(size_t bytes, size_t* got) {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (!block_ || size_ < bytes || size_ / 2 > bytes) return nullptr;
+    void* p = block_;
+    *got = size_;
+    block_ = nullptr;
+    return p;
+  }
+  // keep an idle block (its owner's work has finished); a kept one makes room
+  void give(void* p, size_t bytes) {
+    void* out = p;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (!closed_ && bytes <= max_bytes_) {
+        out = block_;
+        block_ = p;
+        size_ = bytes;
+      }
+    }
+    if (out) (void)hipFree(out);
+  }
+  void set_max(size_t bytes) { max_bytes_ = bytes; }
+  void close() {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      closed_ = true;
+    }
+    release();
+  }
+  bool release() {
+    void* p;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      p = block_;
+      block_ = nullptr;
+    }
+    if (p) (void)hipFree(p);
+    return p != nullptr;
+  }
+  // give back every model's kept block; true if there was one
+  static bool release_all() {
+    std::vector<std::shared_ptr<BlockPool>> live;
+    {
+      std::lock_guard<std::mutex> lk(registry_mu());
+      auto& r = registry();
+      for (size_t i = 0; i < r.size();) {
+        if (auto p = r[i].lock()) {
+          live.push_back(std::move(p));
+          ++i;
+        } else {
+          r.erase(r.begin() + i);
+        }
+      }
+    }
+    bool any = false;
+    for (auto& p : live) any |= p->release();
+    return any;
+  }
+
+ private:
+  static std::mutex& registry_mu() {
+    static std::mutex m;
+    return m;
+  }
+  static std::vector<std::weak_ptr<BlockPool>>& registry() {
+    static std::vector<std::weak_ptr<BlockPool>> r;
+    return r;
+  }
+  std::mutex mu_;
+  void* block_ = nullptr;
+  size_t size_ = 0, max_bytes_ = 0;
+  bool closed_ = false;
+};
+
+void* device_alloc(size_t bytes) {
+  void* p = nullptr;
+  hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    if (BlockPool::release_all()) e = hipMalloc(&p, bytes);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    throw HipError{e, "hipMalloc"};
+  }
+  return p;
+}
+
 struct Allocs {
   std::vector<void*> ptrs;
   ~Allocs() {
@@ -66,15 +174,21 @@ struct Allocs {
   }
   template <typename T>
   T* get(size_t count) {
-    void* p = nullptr;
-    size_t bytes = count * sizeof(T);
-    if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      throw HipError{e, "hipMalloc"};
-    }
+    void* p = device_alloc(std::max<size_t>(count * sizeof(T), 16));
     ptrs.push_back(p);
+    return (T*)p;
+  }
+};
+
+// A set of arrays in one device block: laid out once to measure it (get
+// returns nullptr), then again to hand the addresses out.
+struct Arena {
+  char* base = nullptr;
+  size_t off = 0;
+  template <typename T>
+  T* get(size_t count) {
+    char* p = base ? base + off : nullptr;
+    off += (count * sizeof(T) + 255) & ~(size_t)255;
     return (T*)p;
   }
 };
@@ -261,6 +375,7 @@ struct ssd_model {
   int fwd_xcd[2] = {0, 0};
   unsigned fwd_spin_limit = 0;  // polls before a dependency wait of the persistent pass gives up
   Prof prof;
+  std::shared_ptr<BlockPool> pool = BlockPool::make();  // the last freed session's workspace
   void* scratch = nullptr;  // this model's device's copy of the static workspace (allocation-free runs)
 };
 
@@ -272,7 +387,13 @@ struct ssd_session {
   int max_ctx;         // the caller's bound on P + committed and drafted positions (Lmax rounds it up)
   std::vector<int> f;  // host mirror of the frontier
   bool poisoned = false;
-  Allocs mem;
+  Allocs mem;                        // arrays added after creation
+  std::shared_ptr<BlockPool> pool;   // the model's
+  void* block = nullptr;             // every array below that a session starts with
+  size_t block_bytes = 0;
+  ~ssd_session() {
+    if (block) (void)hipFree(block);
+  }
   int* d_f;
   int* tok;         // [Mmax] working token ids
   unsigned char* acc;
@@ -878,12 +999,7 @@ void size_workspaces(const Dims& dm, const ssd_model* m, int B, int P, int Kmax,
   for (int K = 1; K <= Kmax; ++K) Ks.push_back(K);
   Ks.push_back(P);
   for (int K : Ks) {
-    for (int ctx = 1; ctx <= Lmax; ++ctx) {
-      AttnPlan pc = attn_plan(dm, B, K, ctx, 0);
-      apart = std::max(apart, attn_partials_floats(dm, pc, B));
-      acnt = std::max(acnt, (size_t)B * dm.Hkv * pc.nqg);
-    }
-    AttnPlan pa = attn_plan(dm, B, K, Lmax, 0);
+    const AttnPlan pa = attn_plan_bound(dm, B, K, Lmax);
     apart = std::max(apart, attn_partials_floats(dm, pa, B));
     acnt = std::max(acnt, (size_t)B * dm.Hkv * pa.nqg);
   }
@@ -926,43 +1042,56 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
     int ssq_parts;
     size_workspaces(dm, m, B, P, Kmax, s->Lmax, gpart, gcnt, apart, acnt, ssq_parts);
     const size_t M = s->Mmax;
-    s->d_f = s->mem.get<int>(B);
-    s->tok = s->mem.get<int>(M);
-    s->acc = s->mem.get<unsigned char>(M);
-    s->cnt = s->mem.get<int>((size_t)NCNT_ROUNDS * B);  // [round of the block][B] in image decodes
-    s->amax = s->mem.get<int>(M);
-    s->x = s->mem.get<float>(M * dm.d);
-    // activations: 4 bytes per element (fp32, or hi + lo bf16 planes)
-    s->xn_plane = M * dm.d;
     // q: the tiled bf16 layout pads each KV head's K*g query rows to 32; fp32 uses M*Hq*D of it
     const size_t qcap = (size_t)B * dm.Hkv * q_rows_pad(std::max(P, Kmax), dm.Hq / dm.Hkv) * dm.D;
-    s->q_plane = qcap;
-    s->o_plane = M * dm.Hq * dm.D;
-    s->h_plane = M * dm.dff;
-    s->xn = s->mem.get<char>(M * dm.d * 4);
-    s->ssq_rows_ld = (int)M;
-    s->ssq = s->mem.get<float>((size_t)ssq_parts * M);
-    s->ssq_parts_cap = ssq_parts;
-    s->q = s->mem.get<char>(qcap * 4);
-    s->o = s->mem.get<char>(M * dm.Hq * dm.D * 4);
-    s->h = s->mem.get<char>(M * dm.dff * 4);
-    s->logits = s->mem.get<float>(M * dm.Vimg);
-    s->carry = s->mem.get<float>((size_t)B * dm.Vimg);
-    s->ref = s->mem.get<float>((size_t)B * s->ring * dm.Vimg);
-    s->refstage = s->mem.get<float>((size_t)B * Kmax * dm.Vimg);
-    s->ref_flag = s->mem.get<int>((size_t)B * s->ring);
-    s->kv_layer_elems = (size_t)B * dm.Hkv * s->Lmax * dm.D;
-    s->kc = s->mem.get<char>(s->kv_layer_elems * dm.L * es);
-    s->vc = s->mem.get<char>(s->kv_layer_elems * dm.L * es);
-    s->rope = s->mem.get<float2>((size_t)s->Lmax * (dm.D / 2));
-    s->gpart_cap = gpart;
-    s->gpart = s->mem.get<float>(gpart);
-    s->gcnt_cap = gcnt;
-    s->gcnt = s->mem.get<unsigned>(gcnt);
-    s->apart_cap = apart;
-    s->apart = s->mem.get<float>(apart);
-    s->acnt_cap = acnt;
-    s->acnt = s->mem.get<unsigned>(acnt);
+    auto layout = [&](Arena& mem) {
+      s->d_f = mem.get<int>(B);
+      s->tok = mem.get<int>(M);
+      s->acc = mem.get<unsigned char>(M);
+      s->cnt = mem.get<int>((size_t)NCNT_ROUNDS * B);  // [round of the block][B] in image decodes
+      s->amax = mem.get<int>(M);
+      s->x = mem.get<float>(M * dm.d);
+      // activations: 4 bytes per element (fp32, or hi + lo bf16 planes)
+      s->xn_plane = M * dm.d;
+      s->q_plane = qcap;
+      s->o_plane = M * dm.Hq * dm.D;
+      s->h_plane = M * dm.dff;
+      s->xn = mem.get<char>(M * dm.d * 4);
+      s->ssq_rows_ld = (int)M;
+      s->ssq = mem.get<float>((size_t)ssq_parts * M);
+      s->ssq_parts_cap = ssq_parts;
+      s->q = mem.get<char>(qcap * 4);
+      s->o = mem.get<char>(M * dm.Hq * dm.D * 4);
+      s->h = mem.get<char>(M * dm.dff * 4);
+      s->logits = mem.get<float>(M * dm.Vimg);
+      s->carry = mem.get<float>((size_t)B * dm.Vimg);
+      s->ref = mem.get<float>((size_t)B * s->ring * dm.Vimg);
+      s->refstage = mem.get<float>((size_t)B * Kmax * dm.Vimg);
+      s->ref_flag = mem.get<int>((size_t)B * s->ring);
+      s->kv_layer_elems = (size_t)B * dm.Hkv * s->Lmax * dm.D;
+      s->kc = mem.get<char>(s->kv_layer_elems * dm.L * es);
+      s->vc = mem.get<char>(s->kv_layer_elems * dm.L * es);
+      s->rope = mem.get<float2>((size_t)s->Lmax * (dm.D / 2));
+      s->gpart_cap = gpart;
+      s->gpart = mem.get<float>(gpart);
+      s->gcnt_cap = gcnt;
+      s->gcnt = mem.get<unsigned>(gcnt);
+      s->apart_cap = apart;
+      s->apart = mem.get<float>(apart);
+      s->acnt_cap = acnt;
+      s->acnt = mem.get<unsigned>(acnt);
+    };
+    Arena measure;
+    layout(measure);
+    s->pool = m->pool;
+    s->block = s->pool->take(measure.off, &s->block_bytes);
+    if (!s->block) {
+      s->block_bytes = measure.off;
+      s->block = device_alloc(measure.off);
+    }
+    Arena arena;
+    arena.base = (char*)s->block;
+    layout(arena);
     hipStream_t st = s->stream;
     // the persistent kernel addresses activations and caches through buffer
     // resources: every array must stay below 2 GiB
@@ -1163,6 +1292,9 @@ ssd_status ssd_init_model(const ssd_model_config* cfg, const void* weights, void
     off += (size_t)dm.V * d;
     if ((int64_t)off != numel_of(*cfg)) throw HipError{hipErrorInvalidValue, "layout size mismatch"};
     HIPCHK(hipStreamSynchronize(st));
+    size_t free_b = 0, total_b = 0;
+    HIPCHK(hipMemGetInfo(&free_b, &total_b));
+    m->pool->set_max(total_b / 32);  // 9 GB: the 32-layer 8B model's decode workspace fits
     m->scratch = scratch_of_current_device();  // set-up of the allocation-free head runs
   } catch (HipError& e) {
     delete m;
@@ -1177,7 +1309,11 @@ ssd_status ssd_init_model(const ssd_model_config* cfg, const void* weights, void
 void ssd_free_session(ssd_session* s) {
   if (!s) return;
   if (s->m && s->m->dec == s) s->m->dec = nullptr;
-  (void)hipStreamSynchronize(s->stream);
+  // the workspace stays with the model once the session's work has finished
+  if (hipStreamSynchronize(s->stream) == hipSuccess && !s->poisoned && s->pool) {
+    s->pool->give(s->block, s->block_bytes);
+    s->block = nullptr;
+  }
   delete s;
 }
 
@@ -1189,6 +1325,7 @@ void ssd_free_model(ssd_model* m) {
     m->dec = nullptr;
     delete s;
   }
+  m->pool->close();
   delete m;
 }
 

@@ -308,6 +308,9 @@ struct AttnPlan {
 // grid > 0: a plan for the persistent forward pass (one query tile per work
 // item, items fitting `grid` workgroups where possible)
 AttnPlan attn_plan(const Dims& dm, int B, int K, int max_ctx_now, int xcd, int grid = 0);
+// a plan whose chunk count is at least that of attn_plan (grid 0) for every
+// context up to max_ctx, everything else equal (workspace sizes)
+AttnPlan attn_plan_bound(const Dims& dm, int B, int K, int max_ctx);
 AttnKArgs attn_args(const Dims& dm, const AttnPlan& p, int B, int K, const int* f, const void* q, size_t q_plane,
                     const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, float* partials,
                     unsigned* counters);
