@@ -128,13 +128,14 @@ static void launch_attn(const AttnKArgs& a, hipStream_t st) {
 }
 
 AttnKArgs attn_args(const Dims& dm, const AttnPlan& p, int B, int K, const int* f, const void* q, size_t q_plane,
-                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, float* partials,
+                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, int o_tiled, float* partials,
                     unsigned* counters) {
   AttnKArgs a;
   a.q = (const uint16_t*)q;
   a.kc = (const uint16_t*)kc;
   a.vc = (const uint16_t*)vc;
   a.o = (uint16_t*)o;
+  a.o_tiled = o_tiled;
   a.q_plane = q_plane;
   a.o_plane = o_plane;
   a.heads = B * dm.Hkv;
@@ -164,9 +165,9 @@ int attn_items(const AttnKArgs& a) {
 }
 
 void attention_bf16(const Dims& dm, const AttnPlan& p, int B, int K, const int* f, const void* q, size_t q_plane,
-                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, float* partials,
+                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, int o_tiled, float* partials,
                     unsigned* counters, hipStream_t st) {
-  const AttnKArgs a = attn_args(dm, p, B, K, f, q, q_plane, kc, vc, Lmax, o, o_plane, partials, counters);
+  const AttnKArgs a = attn_args(dm, p, B, K, f, q, q_plane, kc, vc, Lmax, o, o_plane, o_tiled, partials, counters);
   if (dm.D == 128) {
     if (p.qs) launch_attn<128, 2, true>(a, st);
     else if (p.qpw == 2) launch_attn<128, 2>(a, st);

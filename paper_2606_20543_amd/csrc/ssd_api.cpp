@@ -726,7 +726,12 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
   int max_ctx_now = 0;
   for (int b = 0; b < B; ++b) max_ctx_now = std::max(max_ctx_now, s->f[b] + K);
 
-  embed(dm, m->emb, s->tok, M, m->layers[0].g1, s->x, s->xn, s->xn_plane, s->ssq, st);
+  // passes of few rows keep their activations as operand tiles (the persistent
+  // pass stages rows)
+  const int mt = M <= 16 ? 1 : 2;
+  const bool persistent = dm.bf16 && s->fw.on && M <= FWD_MAX_M && m->fwd_grid[mt - 1] > 0;
+  const int tiled = dm.bf16 && M <= ROWS_MAX && !persistent;
+  embed(dm, m->emb, s->tok, M, m->layers[0].g1, s->x, s->xn, s->xn_plane, tiled, s->ssq, st);
   int ssq_parts = 1;
 
   EpiArgs base{};
@@ -750,6 +755,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
   base.q_plane = s->q_plane;
   base.xn_plane = s->xn_plane;
   base.h_plane = s->h_plane;
+  base.tiled = tiled;
 
   if (dm.bf16) {
     // algorithmic bytes: bf16 weights and KV, 4-byte activations (two bf16 planes), fp32 residual
@@ -770,7 +776,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       need(gemm_partials_floats(*gp, M) <= s->gpart_cap && (size_t)gemm_counters(*gp) <= s->gcnt_cap,
            "GEMM plan exceeds the split-K workspace");
     }
-    need(po.n_fb <= s->ssq_parts_cap && p2.n_fb <= s->ssq_parts_cap, "rms partial sums exceed their buffer");
+    need(gemm_parts(po, d) <= s->ssq_parts_cap && gemm_parts(p2, d) <= s->ssq_parts_cap, "rms partial sums exceed their buffer");
     need(attn_partials_floats(dm, pa, B) <= s->apart_cap && (size_t)B * dm.Hkv * pa.nqg <= s->acnt_cap,
          "attention plan exceeds its workspace");
     double attn_bytes = 2.0 * M * dm.Hq * D * A;  // q read + o written
@@ -784,8 +790,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
     const double o_bytes = (double)d * dm.Hq * D * es + (double)M * dm.Hq * D * A + (double)M * d * (8 + A);
     const double gu_bytes = 2.0 * dm.dff * d * es + (double)M * d * A + (double)M * dm.dff * A;
     const double dn_bytes = (double)d * dm.dff * es + (double)M * dm.dff * A + (double)M * d * (8 + A);
-    const int mt = M <= 16 ? 1 : 2;
-    if (s->fw.on && M <= FWD_MAX_M && m->fwd_grid[mt - 1] > 0) {
+    if (persistent) {
       const int G = m->fwd_grid[mt - 1], XF = m->fwd_xcd[mt - 1];
       AttnPlan pf = attn_plan(dm, B, K, max_ctx_now, XF, G);
       const int groups = B * dm.Hkv * pf.nqg;
@@ -807,8 +812,8 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       }
       ++s->fw.epoch;
       a.epoch_base = s->fw.epoch * (unsigned)(dm.L + 1);
-      a.att = attn_args(dm, pf, B, K, s->d_f, s->q, s->q_plane, nullptr, nullptr, s->Lmax, s->o, s->o_plane, s->apart,
-                        s->acnt);
+      a.att = attn_args(dm, pf, B, K, s->d_f, s->q, s->q_plane, nullptr, nullptr, s->Lmax, s->o, s->o_plane, 0,
+                        s->apart, s->acnt);
       a.att_items = attn_items(a.att);
       const int rows_lm = lm_mode == 0 ? M : B;
       const double lm_bytes = (double)dm.Vimg * d * es + (double)rows_lm * d * A + (double)rows_lm * dm.Vimg * 4;
@@ -817,6 +822,11 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       HIPCHK(hipGetLastError());
       return;
     }
+    auto rows_of = [&](const void* p, size_t plane, int ld) {
+      return ActIn{(const uint16_t*)p, plane, ld, 0, 1, tiled};
+    };
+    const ActIn in_x = rows_of(s->xn, s->xn_plane, d), in_o = rows_of(s->o, s->o_plane, dm.Hq * D),
+                in_h = rows_of(s->h, s->h_plane, dm.dff);
     for (int l = 0; l < dm.L; ++l) {
       const LayerW& W = m->layers[l];
       char* kc = (char*)s->kc + (size_t)l * s->kv_layer_elems * es;
@@ -829,11 +839,11 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.kc = kc;
       e.vc = vc;
       m->prof.run(0, qkv_bytes, st, [&] {
-        gemm_bf16(pq, W.wqkv, Nqkv, d, s->xn, s->xn_plane, d, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(pq, W.wqkv, Nqkv, d, in_x, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * Nqkv * d, pq.tile);
       m->prof.run(5, attn_bytes, st, [&] {
-        attention_bf16(dm, pa, B, K, s->d_f, s->q, s->q_plane, kc, vc, s->Lmax, s->o, s->o_plane, s->apart, s->acnt,
-                       st);
+        attention_bf16(dm, pa, B, K, s->d_f, s->q, s->q_plane, kc, vc, s->Lmax, s->o, s->o_plane, tiled, s->apart,
+                       s->acnt, st);
       }, attn_flops);
       e = base;
       e.kind = EPI_RESID;
@@ -841,9 +851,9 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.gnext = W.g2;
       e.ld = d;
       m->prof.run(1, o_bytes, st, [&] {
-        gemm_bf16(po, W.wo, d, dm.Hq * D, s->o, s->o_plane, dm.Hq * D, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(po, W.wo, d, dm.Hq * D, in_o, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * d * dm.Hq * D, po.tile);
-      ssq_parts = po.n_fb;
+      ssq_parts = gemm_parts(po, d);
       e = base;
       e.kind = EPI_SWIGLU;
       e.ssq = s->ssq;
@@ -851,7 +861,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.h = s->h;
       e.ld = dm.dff;
       m->prof.run(2, gu_bytes, st, [&] {
-        gemm_bf16(p13, W.w13, 2 * dm.dff, d, s->xn, s->xn_plane, d, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(p13, W.w13, 2 * dm.dff, d, in_x, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * 2 * dm.dff * d, p13.tile);
       e = base;
       e.kind = EPI_RESID;
@@ -859,9 +869,9 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.gnext = (l + 1 < dm.L) ? m->layers[l + 1].g1 : m->gf;
       e.ld = d;
       m->prof.run(3, dn_bytes, st, [&] {
-        gemm_bf16(p2, W.w2, d, dm.dff, s->h, s->h_plane, dm.dff, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(p2, W.w2, d, dm.dff, in_h, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * d * dm.dff, p2.tile);
-      ssq_parts = p2.n_fb;
+      ssq_parts = gemm_parts(p2, d);
     }
     EpiArgs e = base;
     e.kind = EPI_LOGITS;
@@ -874,7 +884,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       if (gemm_partials_floats(pl, M) > s->gpart_cap || (size_t)gemm_counters(pl) > s->gcnt_cap)
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
       m->prof.run(4, (double)dm.Vimg * d * es + (double)M * d * A + (double)M * dm.Vimg * 4, st, [&] {
-        gemm_bf16(pl, m->wlm, dm.Vimg, d, s->xn, s->xn_plane, d, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(pl, m->wlm, dm.Vimg, d, in_x, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * dm.Vimg * d, pl.tile);
     } else {
       e.ssq_off = K - 1;
@@ -883,8 +893,10 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       if (gemm_partials_floats(pl, B) > s->gpart_cap || (size_t)gemm_counters(pl) > s->gcnt_cap)
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
       m->prof.run(4, (double)dm.Vimg * d * es + (double)B * d * A + (double)B * dm.Vimg * 4, st, [&] {
-        gemm_bf16(pl, m->wlm, dm.Vimg, d, (const uint16_t*)s->xn + (size_t)(K - 1) * d, s->xn_plane, K * d, B, e,
-                  s->gpart, s->gcnt, st);
+        ActIn last = in_x;  // the last row of each sequence
+        last.row0 = K - 1;
+        last.rstep = K;
+        gemm_bf16(pl, m->wlm, dm.Vimg, d, last, B, e, s->gpart, s->gcnt, st);
       }, 2.0 * B * dm.Vimg * d, pl.tile);
     }
   } else {
@@ -982,16 +994,13 @@ void size_workspaces(const Dims& dm, const ssd_model* m, int B, int P, int Kmax,
     return;
   }
   const int Nqkv = (dm.Hq + 2 * dm.Hkv) * dm.D;
-  // every token-tile class a plan can fall in: up to 16, 32 and 64 tokens,
-  // 65..128 (64-token tiles), beyond 128 (tiled, every row-tile count up to
-  // where no plan splits K any more)
   for (int Mc : gemm_row_classes()) {
     for (auto nk : {std::make_pair(Nqkv, dm.d), std::make_pair(dm.d, dm.Hq * dm.D), std::make_pair(2 * dm.dff, dm.d),
                     std::make_pair(dm.d, dm.dff), std::make_pair(dm.Vimg, dm.d)}) {
       GemmPlan p = gemm_plan_bf16(Mc, nk.first, nk.second, 0);  // sizes do not depend on the XCD mapping
       gpart = std::max(gpart, gemm_partials_floats(p, Mc));
       gcnt = std::max(gcnt, (size_t)gemm_counters(p));
-      if (nk.first == dm.d) ssq_parts_max = std::max(ssq_parts_max, std::max(p.n_fb, gemm_max_parts(dm.d)));
+      if (nk.first == dm.d) ssq_parts_max = std::max(ssq_parts_max, gemm_max_parts(dm.d));
     }
   }
   // every block length the session can run, every context up to Lmax
@@ -1041,7 +1050,7 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
     size_t gpart, gcnt, apart, acnt;
     int ssq_parts;
     size_workspaces(dm, m, B, P, Kmax, s->Lmax, gpart, gcnt, apart, acnt, ssq_parts);
-    const size_t M = s->Mmax;
+    const size_t M = s->Mmax, Mp = (M + 15) / 16 * 16;  // tiled activations hold whole groups of 16 rows
     // q: the tiled bf16 layout pads each KV head's K*g query rows to 32; fp32 uses M*Hq*D of it
     const size_t qcap = (size_t)B * dm.Hkv * q_rows_pad(std::max(P, Kmax), dm.Hq / dm.Hkv) * dm.D;
     auto layout = [&](Arena& mem) {
@@ -1052,17 +1061,17 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
       s->amax = mem.get<int>(M);
       s->x = mem.get<float>(M * dm.d);
       // activations: 4 bytes per element (fp32, or hi + lo bf16 planes)
-      s->xn_plane = M * dm.d;
+      s->xn_plane = Mp * dm.d;
       s->q_plane = qcap;
-      s->o_plane = M * dm.Hq * dm.D;
-      s->h_plane = M * dm.dff;
-      s->xn = mem.get<char>(M * dm.d * 4);
+      s->o_plane = Mp * dm.Hq * dm.D;
+      s->h_plane = Mp * dm.dff;
+      s->xn = mem.get<char>(Mp * dm.d * 4);
       s->ssq_rows_ld = (int)M;
       s->ssq = mem.get<float>((size_t)ssq_parts * M);
       s->ssq_parts_cap = ssq_parts;
       s->q = mem.get<char>(qcap * 4);
-      s->o = mem.get<char>(M * dm.Hq * dm.D * 4);
-      s->h = mem.get<char>(M * dm.dff * 4);
+      s->o = mem.get<char>(Mp * dm.Hq * dm.D * 4);
+      s->h = mem.get<char>(Mp * dm.dff * 4);
       s->logits = mem.get<float>(M * dm.Vimg);
       s->carry = mem.get<float>((size_t)B * dm.Vimg);
       s->ref = mem.get<float>((size_t)B * s->ring * dm.Vimg);
@@ -1096,8 +1105,8 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
     // the persistent kernel addresses activations and caches through buffer
     // resources: every array must stay below 2 GiB
     const size_t lim = (size_t)1 << 31;
-    const bool fits = s->kv_layer_elems * es < lim && M * dm.d * 4 < lim && qcap * 4 < lim &&
-                      M * dm.Hq * dm.D * 4 < lim && M * dm.dff * 4 < lim && M * dm.Vimg * 4 < lim &&
+    const bool fits = s->kv_layer_elems * es < lim && Mp * dm.d * 4 < lim && qcap * 4 < lim &&
+                      Mp * dm.Hq * dm.D * 4 < lim && Mp * dm.dff * 4 < lim && M * dm.Vimg * 4 < lim &&
                       (size_t)ssq_parts * M * 4 < lim;
     if (dm.bf16 && (m->fwd_grid[0] > 0 || m->fwd_grid[1] > 0) && B <= FWD_MAX_M && fits) {
       auto& fw = s->fw;
@@ -1381,6 +1390,7 @@ struct HeadWork {
   size_t xn_plane = 0;
   float* ssq = nullptr;    // [parts][rows]
   int ssq_cap = 0, rows = 0;
+  int plane_rows = 0;      // rows the planes of z, xn and hb hold (tiled layouts need whole groups of 16)
   void* hb = nullptr;      // [R][m] split planes
   size_t hb_plane = 0;
   float* logits = nullptr; // [R][V_img]
@@ -1456,12 +1466,16 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     e.ld = dm.Vimg;
     gemm_f32((const float*)m->wlm, dm.Vimg, d, (const float*)w.xn, d, R, e, st);
   } else {
-    draft_input(hin, m->emb, tok, R, d, w.z, w.z_plane, st);
+    base.tiled = R <= ROWS_MAX && (R + 15) / 16 * 16 <= w.plane_rows;
+    auto rows_of = [&](const void* p, size_t plane, int ld) {
+      return ActIn{(const uint16_t*)p, plane, ld, 0, 1, base.tiled};
+    };
+    draft_input(hin, m->emb, tok, R, d, w.z, w.z_plane, base.tiled, st);
     const int X = m->xcd;
     auto plan = [&](int N, int K) {
       GemmPlan p = gemm_plan_bf16(R, N, K, X);
       if (gemm_partials_floats(p, R) > w.gpart_cap || (size_t)gemm_counters(p) > w.gcnt_cap ||
-          (N == d && p.n_fb > w.ssq_cap))
+          (N == d && gemm_parts(p, N) > w.ssq_cap))
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the draft head's workspace"};
       return p;
     };
@@ -1471,30 +1485,30 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     e.kind = EPI_RESID;
     e.gnext = h->g;
     e.ld = d;
-    gemm_bf16(p0, h->w0, d, 2 * d, w.z, w.z_plane, 2 * d, R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p0, h->w0, d, 2 * d, rows_of(w.z, w.z_plane, 2 * d), R, e, w.gpart, w.gcnt, st);
     // SwiGLU(n / rms(u))
     GemmPlan p1 = plan(2 * mi, d);
     e = base;
     e.kind = EPI_SWIGLU;
     e.ssq = w.ssq;
-    e.ssq_parts = p0.n_fb;
+    e.ssq_parts = gemm_parts(p0, d);
     e.ld = mi;
-    gemm_bf16(p1, h->w13, 2 * mi, d, w.xn, w.xn_plane, d, R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p1, h->w13, 2 * mi, d, rows_of(w.xn, w.xn_plane, d), R, e, w.gpart, w.gcnt, st);
     // h_hat = u + W2 (...); n = g_f * h_hat for the output layer
     GemmPlan p2 = plan(d, mi);
     e = base;
     e.kind = EPI_RESID;
     e.gnext = m->gf;
     e.ld = d;
-    gemm_bf16(p2, h->w2, d, mi, w.hb, w.hb_plane, mi, R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p2, h->w2, d, mi, rows_of(w.hb, w.hb_plane, mi), R, e, w.gpart, w.gcnt, st);
     // GenHead(RMSNorm(h_hat)) over the image codes
     GemmPlan p3 = plan(dm.Vimg, d);
     e = base;
     e.kind = EPI_LOGITS;
     e.ssq = w.ssq;
-    e.ssq_parts = p2.n_fb;
+    e.ssq_parts = gemm_parts(p2, d);
     e.ld = dm.Vimg;
-    gemm_bf16(p3, m->wlm, dm.Vimg, d, w.xn, w.xn_plane, d, R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p3, m->wlm, dm.Vimg, d, rows_of(w.xn, w.xn_plane, d), R, e, w.gpart, w.gcnt, st);
   }
   first_token(R, dm.Vimg, dm.img_lo, w.logits, SSD_GREEDY, 0, 1.0, 0, nullptr, w.out, 1, st);
   HIPCHK(hipGetLastError());
@@ -1598,7 +1612,7 @@ ssd_status ssd_draft_head_init(ssd_model* m, int32_t mi, const void* weights, in
         GemmPlan p = gemm_plan_bf16(Mc, nk.first, nk.second, 0);
         gpart = std::max(gpart, gemm_partials_floats(p, Mc));
         gcnt = std::max(gcnt, (size_t)gemm_counters(p));
-        if (nk.first == d) parts = std::max(parts, std::max(p.n_fb, gemm_max_parts(d)));
+        if (nk.first == d) parts = std::max(parts, gemm_max_parts(d));
       }
     }
     HeadWork& w = h->work;
@@ -1613,13 +1627,15 @@ ssd_status ssd_draft_head_init(ssd_model* m, int32_t mi, const void* weights, in
     w.out = h->mem.get<int>(R);
     w.f0 = h->mem.get<int>(1);
     w.hin = h->mem.get<float>(R * d);
-    w.z_plane = R * 2 * d;
-    w.z = h->mem.get<char>(R * 2 * d * 4);
+    const size_t Rp = (R + 15) / 16 * 16;
+    w.plane_rows = (int)Rp;
+    w.z_plane = Rp * 2 * d;
+    w.z = h->mem.get<char>(Rp * 2 * d * 4);
     w.x = h->mem.get<float>(R * d);
-    w.xn_plane = R * d;
-    w.xn = h->mem.get<char>(R * d * 4);
-    w.hb_plane = R * mi;
-    w.hb = h->mem.get<char>(R * mi * 4);
+    w.xn_plane = Rp * d;
+    w.xn = h->mem.get<char>(Rp * d * 4);
+    w.hb_plane = Rp * mi;
+    w.hb = h->mem.get<char>(Rp * mi * 4);
     w.logits = h->mem.get<float>(R * dm.Vimg);
     fill_u32(w.gcnt, gcnt, 0u, st);
     fill_u32((unsigned*)w.f0, 1, 0u, st);
@@ -1687,16 +1703,25 @@ ssd_status ssd_draft_head_run_noalloc(ssd_draft_head* h, int32_t R, const float*
       GemmPlan pl = gemm_plan_bf16(R, p.first, p.second, m->xcd);
       gpart = std::max(gpart, gemm_partials_floats(pl, R));
       gcnt = std::max(gcnt, (size_t)gemm_counters(pl));
-      if (p.first == d) parts = std::max(parts, pl.n_fb);
+      if (p.first == d) parts = std::max(parts, gemm_parts(pl, d));
     }
   }
   const size_t r = (size_t)R;
-  const size_t sz[12] = {gcnt * 4, 4, r * 4, r * 4, r * d * 4, r * 2 * d * 4, r * d * 4, r * d * 4,
-                         (size_t)parts * r * 4, r * mi * 4, r * dm.Vimg * 4, gpart * 4};
+  size_t rp = dm.bf16 && R <= ROWS_MAX ? (r + 15) / 16 * 16 : r;  // rows of the planes (tiled layouts)
   size_t off[12], need = 0;
-  for (int i = 0; i < 12; ++i) {
-    off[i] = need;
-    need += (sz[i] + 255) & ~(size_t)255;
+  auto carve = [&]() {
+    const size_t sz[12] = {gcnt * 4, 4, r * 4, r * 4, r * d * 4, rp * 2 * d * 4, r * d * 4, rp * d * 4,
+                           (size_t)parts * r * 4, rp * mi * 4, r * dm.Vimg * 4, gpart * 4};
+    need = 0;
+    for (int i = 0; i < 12; ++i) {
+      off[i] = need;
+      need += (sz[i] + 255) & ~(size_t)255;
+    }
+  };
+  carve();
+  if (need > NOALLOC_SCRATCH_BYTES && rp > r) {  // without the padding (row-major planes) it may still fit
+    rp = r;
+    carve();
   }
   if (need > NOALLOC_SCRATCH_BYTES)
     return fail(SSD_E_INVAL, "R = %d rows need %zu bytes of workspace; the static workspace holds %zu", R, need,
@@ -1711,14 +1736,15 @@ ssd_status ssd_draft_head_run_noalloc(ssd_draft_head* h, int32_t R, const float*
   w.out = (int*)(base + off[3]);
   w.hin = (float*)(base + off[4]);
   w.z = base + off[5];
-  w.z_plane = r * 2 * d;
+  w.plane_rows = (int)rp;
+  w.z_plane = rp * 2 * d;
   w.x = (float*)(base + off[6]);
   w.xn = base + off[7];
-  w.xn_plane = r * d;
+  w.xn_plane = rp * d;
   w.ssq = (float*)(base + off[8]);
   w.ssq_cap = parts;
   w.hb = base + off[9];
-  w.hb_plane = r * mi;
+  w.hb_plane = rp * mi;
   w.logits = (float*)(base + off[10]);
   w.gpart = (float*)(base + off[11]);
   w.gpart_cap = gpart;

@@ -3,6 +3,8 @@
 // Data layout in HBM (all row-major unless stated):
 //   residual x        fp32 [M][d]
 //   xn                act [M][d]              g * x: the GEMM input after an RMSNorm
+//                     (act arrays: 16x32 tiles in passes of at most ROWS_MAX
+//                     rows, row-major in larger ones; see act_index)
 //   ssq               fp32 [parts][Mmax]      partial sums of x^2 per token (producer feature blocks)
 //   q                 act [B][Hkv][rows_pad x D as 16x32 tiles]   bf16 models; query row
 //                     r = head_in_group * K + k, rows_pad = K*g rounded up to 32
@@ -79,6 +81,16 @@ struct EpiArgs {
   int ld;                // x / xn / h / logits row length
   // plane strides (elements) of the split activation buffers
   size_t q_plane, xn_plane, h_plane;
+  int tiled;             // layout of xn and h (act_index)
+};
+
+// Input rows of a projection: token t is row row0 + t * rstep of a split
+// activation array of `ld` columns (act_index), the lo plane `plane` elements
+// after the hi plane.
+struct ActIn {
+  const uint16_t* p;
+  size_t plane;
+  int ld, row0, rstep, tiled;
 };
 
 // Device model (owned by ssd_model)
@@ -98,6 +110,14 @@ __host__ __device__ inline size_t tile16x32_index(int row, int col, int cols) {
   return ((size_t)(row >> 4) * (cols >> 5) + (col >> 5)) * 512 + (size_t)((((col & 31) >> 3) << 4) + (row & 15)) * 8 +
          (col & 7);
 }
+// Element (row, col) of a plane of a split activation array of `cols` columns:
+// 16x32 tiles for the few-row kernel, whose token fragments are then one
+// contiguous KiB each; row-major for the tiled kernels, which copy rows of a
+// K stage into LDS (the tiled layout measured the same there).  Tiled arrays
+// hold whole groups of 16 rows.
+__host__ __device__ inline size_t act_index(int tiled, int row, int col, int cols) {
+  return tiled ? tile16x32_index(row, col, cols) : (size_t)row * cols + col;
+}
 // Element (d, key) of the transposed V cache [D][Lmax] as 16x32 tiles of
 // (16 dims x 32 keys), keys of a tile permuted so that lane d%16 + 16*g holds
 // keys 4g..4g+3 and 16+4g..16+4g+3 (the A operand of O^T = V^T P^T whose
@@ -110,20 +130,24 @@ __host__ __device__ inline size_t vtile_index(int d, int key, int Lmax) {
 // query rows per KV head padded for the tiled q layout
 __host__ __device__ inline int q_rows_pad(int K, int g) { return ((K * g + 31) / 32) * 32; }
 
-// Most partial sums of x^2 per token a GEMM's 1/rms prologue accepts (the
-// producing GEMM writes one per 64-feature block: d_model <= 8192).
+// Most partial sums of x^2 per token the persistent pass's 1/rms prologue
+// accepts (one per 64-feature block: d_model <= 8192).
 constexpr int GEMM_RMS_MAX_PARTS = 128;
+// Most rows of a pass whose projections run on the few-row kernel
+constexpr int ROWS_MAX = 64;
 
-// GEMM launch plan for one (M, N, K) problem.
+// GEMM launch plan for one (M, N, K) problem.  tile 0: the few-row kernel, 16 NT
+// features and 16 MT rows per workgroup, K split S ways (n_fb counts 64-feature
+// groups; see gemm_parts).
 struct GemmPlan {
   int MT, NT, KCB;  // token tiles, feature tiles per wave, 32-k blocks per chunk
-  int WV;           // waves per workgroup (4, or 6..16 for one-burst wide workgroups)
+  int WV;           // waves per workgroup
   int S;            // K splits
   int n_fb;         // feature blocks
   int kchunks;      // chunks per split
-  int bn;           // features per workgroup
+  int bn;           // features per feature block
   int xcd;          // >0: workgroups that reduce together share one XCD (n XCDs); 0: fenced reduction
-  int tile;         // 1: tiled kernel for more than 64 rows (128-row tiles, K split only to fill the CUs);
+  int tile;         // 1: tiled kernel for more than ROWS_MAX rows (128-row tiles, K split only to fill the CUs);
                     // 3: 128 x 256 tiles of eight waves, both operands by LDS DMA
   int m_tiles;      // tiled: 128-row tiles
   int depth;        // tiled: register stages of the K pipeline (2 or 4)
@@ -131,15 +155,18 @@ struct GemmPlan {
   int tail_S;       //   in a second launch with K split tail_S ways (a last round that would run part empty)
   int tail_nt;      //   3: the rest as whole 128 x 192 tiles instead (tail_S 1), else 0
 };
-// split-K arrival counters a plan uses (tiled plans: one per output tile, when split)
+// feature blocks of a plan's workgroups for output width N: the x^2 parts per
+// row that a residual projection writes
+inline int gemm_parts(const GemmPlan& p, int N) { return p.tile ? p.n_fb : (N / 16 + p.NT - 1) / p.NT; }
+// arrival counters a plan uses when K is split (one per output tile)
 inline int gemm_counters(const GemmPlan& p) {
   if (p.tile && p.tail_fb) return p.tail_nt ? 0 : (p.n_fb - p.tail_fb) * p.m_tiles;
-  return p.tile ? (p.S > 1 ? p.n_fb * p.m_tiles : 0) : p.n_fb;
+  if (p.S <= 1) return 0;
+  return p.tile ? p.n_fb * p.m_tiles : gemm_parts(p, p.n_fb * p.bn);
 }
-// Row counts that cover every plan class: up to 16, 32 and 64 rows, 65..128
-// (one 128-row tile, or 64-row streaming tiles for shapes the tiled kernel
-// does not take) and each count of 128-row tiles up to 256 (a split plan has
-// fewer than 256 output tiles).  Sizing a workspace over these bounds every
+// Row counts that cover every plan class: the few-row kernel's (up to 16, 32,
+// 48 and 64 rows), 65..128 and each count of 128-row tiles up to 256 (a
+// split plan has fewer than 256 output tiles).  Sizing a workspace over these bounds every
 // plan of any row count.
 inline std::vector<int> gemm_row_classes() {
   std::vector<int> v = {1, 16, 17, 32, 33, 64, 65, 128};
@@ -147,8 +174,8 @@ inline std::vector<int> gemm_row_classes() {
   return v;
 }
 // most per-row partial sums of x^2 a plan of output width N writes (one per
-// feature block; no plan has blocks narrower than 64 features)
-inline int gemm_max_parts(int N) { return (N + 63) / 64; }
+// feature block; no plan has blocks narrower than 16 features)
+inline int gemm_max_parts(int N) { return (N + 15) / 16; }
 
 // Cross-workgroup reductions (split-K partials, attention key chunks).  The
 // workgroups of one reduction group are mapped onto one XCD, so their
@@ -204,9 +231,22 @@ inline void launch_timed(Kern kernel, dim3 grid, dim3 block, hipStream_t st, Arg
 // ---- launchers (kernels_*.hip) ----
 GemmPlan gemm_plan_bf16(int M, int N, int K, int xcd);
 size_t gemm_partials_floats(const GemmPlan& p, int M);
-// y = W x for split inputs in[M][K] (row stride ld_in, lo plane in_plane elements after hi); epilogue per `epi`.
-void gemm_bf16(const GemmPlan& p, const void* Wpacked, int N, int K, const void* in, size_t in_plane, int ld_in,
-               int M, const EpiArgs& epi, float* partials, unsigned* counters, hipStream_t st);
+GemmPlan gemm_rows_plan(int M, int N, int K, int xcd);  // (part of gemm_plan_bf16)
+// y = W x for M split input rows; epilogue per `epi`.
+void gemm_bf16(const GemmPlan& p, const void* Wpacked, int N, int K, const ActIn& in, int M, const EpiArgs& epi,
+               float* partials, unsigned* counters, hipStream_t st);
+// few-row kernel (gemm_rows.h)
+struct RowsKArgs {
+  const void* W;
+  int N, KB;               // KB = K / 32
+  int n_fb, S, xcd;        // workgroups: feature blocks x K splits
+  ActIn in;
+  int M, t0;
+  float* part;
+  unsigned* counters;
+  EpiArgs epi;
+};
+void gemm_rows(int MT, int NT, const RowsKArgs& a, hipStream_t st);
 // fp32 projection; a residual epilogue leaves its per-token sums of x^2 in
 // epi.ssq_out and the call returns their part count (0 for other epilogues)
 int gemm_f32(const float* W, int N, int K, const float* in, int ld_in, int M, const EpiArgs& epi, hipStream_t st);
@@ -216,9 +256,9 @@ inline int f32_feature_blocks(int N) { return (N + 15) / 16; }
 void pack_bf16_tiles(const uint16_t* src, const int* rowmap, int N, int K, void* dst, hipStream_t st);
 void gather_rows_f32(const float* src, const int* rowmap, int N, int K, float* dst, hipStream_t st);
 
-// x[t] = E[tok[t]]; xn = g * x (split planes for bf16 models); ssq[t] = sum x^2 (one part)
+// x[t] = E[tok[t]]; xn = g * x (split planes for bf16 models, laid out by act_index); ssq[t] = sum x^2 (one part)
 void embed(const Dims& dm, const void* emb, const int* tok, int M, const float* g, float* x, void* xn,
-           size_t xn_plane, float* ssq, hipStream_t st);
+           size_t xn_plane, int tiled, float* ssq, hipStream_t st);
 // fp32 path: ssq[t] = sum x^2 of row t (one part)
 void norm_rows_f32(const float* x, int M, int d, float* ssq, hipStream_t st);
 
@@ -226,7 +266,8 @@ struct AttnKArgs {
   const uint16_t* q;   // [B][Hkv][qrows_pad x D tiles], hi plane then lo plane (q_plane elements apart)
   const uint16_t* kc;  // [B][Hkv][Lmax x D tiles]
   const uint16_t* vc;  // [B][Hkv][D x Lmax tiles, keys permuted]
-  uint16_t* o;         // [B*K][Hq*D], hi plane then lo plane (o_plane elements apart)
+  uint16_t* o;         // [B*K][Hq*D], hi plane then lo plane (o_plane elements apart; act_index)
+  int o_tiled;
   size_t q_plane, o_plane;
   float* opart;        // [groups][nchunk][QPW*16][D]   chunk partial O (relative to the chunk max)
   float2* spart;       // [groups][nchunk][QPW*16]      chunk (max, sum), log2 domain
@@ -312,12 +353,12 @@ AttnPlan attn_plan(const Dims& dm, int B, int K, int max_ctx_now, int xcd, int g
 // context up to max_ctx, everything else equal (workspace sizes)
 AttnPlan attn_plan_bound(const Dims& dm, int B, int K, int max_ctx);
 AttnKArgs attn_args(const Dims& dm, const AttnPlan& p, int B, int K, const int* f, const void* q, size_t q_plane,
-                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, float* partials,
+                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, int o_tiled, float* partials,
                     unsigned* counters);
 int attn_items(const AttnKArgs& a);  // work items (workgroups) of one attention call
 size_t attn_partials_floats(const Dims& dm, const AttnPlan& p, int B);
 void attention_bf16(const Dims& dm, const AttnPlan& p, int B, int K, const int* f, const void* q, size_t q_plane,
-                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, float* partials,
+                    const void* kc, const void* vc, int Lmax, void* o, size_t o_plane, int o_tiled, float* partials,
                     unsigned* counters, hipStream_t st);
 void attention_f32(const Dims& dm, int B, int K, const int* f, const float* q, const float* kc, const float* vc,
                    int Lmax, float* o, hipStream_t st);
@@ -383,9 +424,9 @@ void xcc_probe(int* out, int n_wg, hipStream_t st);
 // references of block positions f+k <- src rows (b * rows_per_b + k); only_new keeps existing references
 void set_ref_rows(int B, int K, int rows_per_b, int Vimg, const float* src, const int* f, float* ref, int* ref_flag,
                   int ring, int only_new, hipStream_t st);
-// z = [h; e] split planes [R][2d] (plane elements apart) for a draft head
+// z = [h; e] split planes [R][2d] (plane elements apart, act_index) for a draft head
 void draft_input_f32(const float* h, const float* emb, const int* tok, int R, int d, float* z, hipStream_t st);
-void draft_input(const float* h, const void* emb, const int* tok, int R, int d, void* z, size_t plane,
+void draft_input(const float* h, const void* emb, const int* tok, int R, int d, void* z, size_t plane, int tiled,
                  hipStream_t st);
 // guided logits l_u + w (l_c - l_u): rows [Bi][K] from the pass's [2*Bi][K] logits
 // (K may be 0) and the carry [Bi] from [2*Bi]

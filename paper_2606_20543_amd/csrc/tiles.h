@@ -238,37 +238,16 @@ __device__ __forceinline__ void load_a(u32x4 (&ra)[NT][KCB], const u32x4* W, int
     }
 }
 
-template <int MT, int KCB, int NTH = 256>
+template <int MT, int KCB>
 struct XStage {
   static constexpr int MP = MT * 16;
   static constexpr int KC = KCB * 32;
   static constexpr int LD = KC + 8;          // bf16 per LDS row (16-byte pad)
   static constexpr int PL = MP * LD;         // one plane
-  static constexpr int CG = KC / 8;          // 16-byte column groups per row
-  static constexpr int RSTEP = NTH / CG;     // rows covered per pass (NTH threads)
-  static constexpr int PASSES = (MP + RSTEP - 1) / RSTEP;
 };
 
-// x chunk (both planes) -> registers
-template <int MT, int KCB, int NP, class Mem = PlainMem, int NTH = 256>
-__device__ __forceinline__ void load_x(u32x4 (&rx)[2][NP], const uint16_t* in, size_t plane, int ld_in, int M,
-                                       int k0) {
-  using X = XStage<MT, KCB, NTH>;
-  const int cg = threadIdx.x % X::CG, r0 = threadIdx.x / X::CG;
-  // token rows past M repeat row M-1: no branch around the loads (so they
-  // issue back to back); the results of those rows are never stored
-#pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    const int r = r0 + p * X::RSTEP;
-    const int rc = r < M ? r : M - 1;
-    const size_t off = ((size_t)rc * ld_in + k0 + cg * 8) * 2;
-    rx[0][p] = Mem::ld16(in, off);
-    rx[1][p] = Mem::ld16(in, off + plane * 2);
-  }
-}
-
-// The same chunk straight into LDS (gfx950 LDS DMA, 16 bytes per lane, no
-// registers): wave w copies rows w, w + 4, ... of both planes, one 1 KiB row
+// x chunk (both planes) straight into LDS (gfx950 LDS DMA, 16 bytes per lane,
+// no registers): wave w copies rows w, w + 4, ... of both planes, one 1 KiB row
 // per instruction.  AUX: cache policy of the global reads.  The caller waits
 // for vmcnt(0) and then barriers before the LDS is read.
 template <int MT, int KCB, int AUX, int NW = 4>
@@ -284,20 +263,6 @@ __device__ __forceinline__ void load_x_lds(uint16_t* xs, const uint16_t* in, siz
                                      (void __attribute__((address_space(3)))*)(xs + r * X::LD), 16, 0, AUX);
     __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(src + plane),
                                      (void __attribute__((address_space(3)))*)(xs + X::PL + r * X::LD), 16, 0, AUX);
-  }
-}
-
-template <int MT, int KCB, int NP, int NTH = 256>
-__device__ __forceinline__ void store_x(const u32x4 (&rx)[2][NP], uint16_t* xs) {
-  using X = XStage<MT, KCB, NTH>;
-  const int cg = threadIdx.x % X::CG, r0 = threadIdx.x / X::CG;
-#pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    int r = r0 + p * X::RSTEP;
-    if (X::PASSES * X::RSTEP == X::MP || r < X::MP) {
-      *(u32x4*)(xs + r * X::LD + cg * 8) = rx[0][p];
-      *(u32x4*)(xs + X::PL + r * X::LD + cg * 8) = rx[1][p];
-    }
   }
 }
 
@@ -560,8 +525,9 @@ __device__ __forceinline__ void epi_store(const EpiArgs& e, const floatx4 (&acc)
           uint32_t h0, l0, h1, l1;
           split2(g.x * xv.x, g.y * xv.y, h0, l0);
           split2(g.z * xv.z, g.w * xv.w, h1, l1);
-          Mem::st8(e.xn, i * 2, make_uint2(h0, h1));
-          Mem::st8(e.xn, (e.xn_plane + i) * 2, make_uint2(l0, l1));
+          const size_t j = act_index(e.tiled, t, n, e.ld);
+          Mem::st8(e.xn, j * 2, make_uint2(h0, h1));
+          Mem::st8(e.xn, (e.xn_plane + j) * 2, make_uint2(l0, l1));
           sq[mt] += (xv.x * xv.x + xv.y * xv.y) + (xv.z * xv.z + xv.w * xv.w);
           break;
         }
@@ -571,7 +537,7 @@ __device__ __forceinline__ void epi_store(const EpiArgs& e, const floatx4 (&acc)
           const float s0 = g0 / (1.0f + expf(-g0)), s1 = g1 / (1.0f + expf(-g1));
           uint32_t hi, lo;
           split2(s0 * u0, s1 * u1, hi, lo);
-          const size_t i = (size_t)t * e.ld + (n >> 1);
+          const size_t i = act_index(e.tiled, t, n >> 1, e.ld);
           Mem::st4(e.h, i * 2, hi);
           Mem::st4(e.h, (e.h_plane + i) * 2, lo);
           break;
@@ -586,12 +552,19 @@ __device__ __forceinline__ void epi_store(const EpiArgs& e, const floatx4 (&acc)
 }
 
 
-// hi/lo bf16 planes of four consecutive fp32 values
+// hi/lo bf16 planes of four consecutive fp32 values v * f: hi = bf16(v f), lo =
+// bf16(v f - hi) with the product unrounded (one fused multiply-add, spelled
+// out so that the bits do not depend on what the compiler fuses)
 template <class Mem = PlainMem>
-__device__ __forceinline__ void store_split4(uint16_t* base, size_t i, size_t plane, floatx4 v) {
+__device__ __forceinline__ void store_split4(uint16_t* base, size_t i, size_t plane, floatx4 v, float f) {
+  auto pair = [f](float a, float b, uint32_t& hi, uint32_t& lo) {
+    hi = cvt2bf(a * f, b * f);
+    lo = cvt2bf(__builtin_fmaf(a, f, -__uint_as_float(hi << 16)),
+                __builtin_fmaf(b, f, -__uint_as_float(hi & 0xFFFF0000u)));
+  };
   uint2 w, x;
-  split2(v[0], v[1], w.x, x.x);
-  split2(v[2], v[3], w.y, x.y);
+  pair(v[0], v[1], w.x, x.x);
+  pair(v[2], v[3], w.y, x.y);
   Mem::st8(base, i * 2, w);
   Mem::st8(base, (i + plane) * 2, x);
 }
@@ -998,14 +971,33 @@ __device__ __forceinline__ int attn_unit(const AttnKArgs& a, int item, float* sm
   }
   __syncthreads();
 
-  // merge the waves: thread owns float4 slots idx = tid + NTH * i (row r, dims 4*d4..)
+  // float4 slot ic of the output: row r, dims 4*d4 ..; consecutive slots walk a
+  // row, or (tiled output) the two halves of a tile's 16-byte pieces down the rows
+  auto slot = [&](int ic, int& r, int& d4) {
+    if (a.o_tiled) {
+      r = (ic >> 1) % ROWS;
+      d4 = ((ic >> 1) / ROWS) * 2 + (ic & 1);
+    } else {
+      r = ic / (D / 4);
+      d4 = ic - r * (D / 4);
+    }
+  };
+  // output rows of the query rows of this workgroup
+  auto store_row = [&](int r, int d4, floatx4 v, float f) {
+    const int rg = rbase + r;
+    if (rg >= a.rows) return;
+    const int j = rg / a.K, k = rg - j * a.K;
+    store_split4<Mem>(a.o, act_index(a.o_tiled, b * a.K + k, (hkv * a.g + j) * D + 4 * d4, a.Hq * D), a.o_plane, v,
+                      f);
+  };
+  // merge the waves: thread owns slots tid + NTH * i
   floatx4 acc[NV];
   float Lr[NV], Mr[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int idx = threadIdx.x + NTH * i;
-    const int ic = idx < NOUT ? idx : NOUT - 1;
-    const int r = ic / (D / 4), d4 = ic - r * (D / 4);
+    int r, d4;
+    slot(idx < NOUT ? idx : NOUT - 1, r, d4);
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NWM; ++w) M = fmaxf(M, sm_m[w * ROWS + r]);
@@ -1028,12 +1020,9 @@ __device__ __forceinline__ int attn_unit(const AttnKArgs& a, int item, float* sm
     for (int i = 0; i < NV; ++i) {
       const int idx = threadIdx.x + NTH * i;
       if (idx >= NOUT) continue;
-      const int r = idx / (D / 4), d4 = idx - r * (D / 4);
-      const int rg = rbase + r;
-      if (rg >= a.rows) continue;
-      const int j = rg / a.K, k = rg - j * a.K;
-      const size_t oi = ((size_t)b * a.K + k) * (a.Hq * D) + (hkv * a.g + j) * D + 4 * d4;
-      store_split4<Mem>(a.o, oi, a.o_plane, acc[i] * (1.f / Lr[i]));
+      int r, d4;
+      slot(idx, r, d4);
+      store_row(r, d4, acc[i], 1.f / Lr[i]);
     }
     return grp_id;
   }
@@ -1048,7 +1037,8 @@ __device__ __forceinline__ int attn_unit(const AttnKArgs& a, int item, float* sm
       if (idx >= NOUT) continue;
       const floatx4 v = acc[i];
       PMem::stf4(Op, (size_t)idx * 16, make_float4(v[0], v[1], v[2], v[3]));
-      const int r = idx / (D / 4), d4 = idx - r * (D / 4);
+      int r, d4;
+      slot(idx, r, d4);
       if (d4 == 0) PMem::stf2(a.spart, ((gbase + c) * ROWS + r) * 8, make_float2(Mr[i], Lr[i]));
     }
   }
@@ -1108,7 +1098,9 @@ __device__ __forceinline__ int attn_unit(const AttnKArgs& a, int item, float* sm
         const int idx = threadIdx.x + NTH * (i0 + j);
         const int ic = idx < NOUT ? idx : NOUT - 1;
         g4[j] = PMem::ldf4(G, ((size_t)cc * NOUT + ic) * 16);
-        wt[j] = cl[cc * ROWS + ic / (D / 4)];
+        int r, d4;
+        slot(ic, r, d4);
+        wt[j] = cl[cc * ROWS + r];
       }
       __builtin_amdgcn_sched_barrier(0);  // the batch's loads and weight reads go out before their first use
 #pragma unroll
@@ -1119,12 +1111,9 @@ __device__ __forceinline__ int attn_unit(const AttnKArgs& a, int item, float* sm
   for (int i = 0; i < NV; ++i) {
     const int idx = threadIdx.x + NTH * i;
     if (idx >= NOUT) continue;
-    const int r = idx / (D / 4), d4 = idx - r * (D / 4);
-    const int rg = rbase + r;
-    if (rg >= a.rows) continue;
-    const int j = rg / a.K, k = rg - j * a.K;
-    const size_t oi = ((size_t)b * a.K + k) * (a.Hq * D) + (hkv * a.g + j) * D + 4 * d4;
-    store_split4<Mem>(a.o, oi, a.o_plane, v[i] * (1.f / sm_l[r]));
+    int r, d4;
+    slot(idx, r, d4);
+    store_row(r, d4, v[i], 1.f / sm_l[r]);
   }
   return grp_id;
 }
