@@ -87,9 +87,9 @@ __device__ __forceinline__ float epi_pair(const EpiArgs& e, int t, int n, float 
     }
     case EPI_RESID: {
       size_t i = (size_t)t * e.ld + n;
-      float2 xo = *(const float2*)(e.x + i);
+      float2 xo = e.x ? *(const float2*)(e.x + i) : make_float2(0.f, 0.f);
       float x0 = xo.x + v0, x1 = xo.y + v1;
-      *(float2*)(e.x + i) = make_float2(x0, x1);
+      *(float2*)(e.xo + i) = make_float2(x0, x1);
       st_split<BF>(e.xn, e.xn_plane, i, e.gnext[n] * x0);
       st_split<BF>(e.xn, e.xn_plane, i + 1, e.gnext[n + 1] * x1);
       return x0 * x0 + x1 * x1;
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmKArgs a) {
           const floatx4 v = acc[nt][mt];
           const float4 xo = op.a[nt][mt], g = op.g[nt];
           const float4 xv = make_float4(xo.x + v[0], xo.y + v[1], xo.z + v[2], xo.w + v[3]);
-          if (row < Mw) *(float4*)(e.x + (size_t)(t0w + row) * e.ld + (nb0 + nt) * 16 + nq) = xv;
+          if (row < Mw) *(float4*)(e.xo + (size_t)(t0w + row) * e.ld + (nb0 + nt) * 16 + nq) = xv;
           uint32_t h0, l0, h1, l1;
           split2(g.x * xv.x, g.y * xv.y, h0, l0);
           split2(g.z * xv.z, g.w * xv.w, h1, l1);
@@ -736,7 +736,7 @@ __device__ __forceinline__ void t8_epilogue(const GemmKArgs& a, int fb, int ft, 
           const floatx4 v = acc[nt][mt];
           const float4 xo = op.a[nt][mt], g = op.g[nt];
           const float4 xv = make_float4(xo.x + v[0], xo.y + v[1], xo.z + v[2], xo.w + v[3]);
-          if (row < Mw) *(float4*)(e.x + (size_t)(t0w + row) * e.ld + (nb0 + nt) * 16 + nq) = xv;
+          if (row < Mw) *(float4*)(e.xo + (size_t)(t0w + row) * e.ld + (nb0 + nt) * 16 + nq) = xv;
           uint32_t h0, l0, h1, l1;
           split2(g.x * xv.x, g.y * xv.y, h0, l0);
           split2(g.z * xv.z, g.w * xv.w, h1, l1);
@@ -1301,7 +1301,7 @@ int gemm_f32(const float* W, int N, int K, const float* in, int ld_in, int M, co
   dim3 grid((pairs + 127) / 128, M);
   hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(128), 0, st, W, N, K, in, ld_in, M, epi);
   if (epi.kind != EPI_RESID) return 0;
-  norm_rows_f32(epi.x, M, N, epi.ssq_out, st);
+  norm_rows_f32(epi.xo, M, N, epi.ssq_out, st);
   return 1;
 }
 

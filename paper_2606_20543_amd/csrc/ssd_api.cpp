@@ -182,6 +182,20 @@ struct Allocs {
 
 // A set of arrays in one device block: laid out once to measure it (get
 // returns nullptr), then again to hand the addresses out.
+// The current device's own memory (not managed, not another GPU's): kernels may
+// read and write a caller's array there in place of a copy.  Vector accesses
+// need it aligned.
+bool is_local_ptr(const void* p, size_t align) {
+  if (!p || ((uintptr_t)p & (align - 1))) return false;
+  hipPointerAttribute_t attr;
+  int dev = -1;
+  if (hipPointerGetAttributes(&attr, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return attr.type == hipMemoryTypeDevice && attr.device == dev;
+}
+
 struct Arena {
   char* base = nullptr;
   size_t off = 0;
@@ -394,7 +408,8 @@ struct ssd_session {
   ~ssd_session() {
     if (block) (void)hipFree(block);
   }
-  int* d_f;
+  int* d_f;          // with ref_flag, gcnt and acnt behind it: cleared together at creation
+  char* zeroed_end;
   int* tok;         // [Mmax] working token ids
   unsigned char* acc;
   int* cnt;
@@ -714,8 +729,23 @@ const FwdPhase* fwd_table(ssd_session* s, int K, int lm_mode, int X, int G, cons
 }
 
 // ---------------- forward pass ----------------
+// Where a pass reads its tokens and leaves its results (nullptr: the session's own arrays).
+struct PassIo {
+  const int* tok = nullptr;  // token ids, rows of tok_stride; tok_rows sequences' worth (TokIn)
+  int tok_stride = 0, tok_rows = 0;
+  float* logits = nullptr;   // [rows][V_img]
+  float* h_pre = nullptr;    // [M][d] (kernel-per-projection passes only)
+  int* zero = nullptr;       // cleared by the pass's first kernel
+  int n_zero = 0;
+};
+
+// a pass whose projections and attention run as one launch
+bool pass_is_persistent(const ssd_session* s, int M) {
+  return s->dm.bf16 && s->fw.on && M <= FWD_MAX_M && s->m->fwd_grid[M <= 16 ? 0 : 1] > 0;
+}
+
 // lm_mode: 0 = logits for all B*K rows; 1 = logits for the last row of each sequence only
-void run_forward(ssd_session* s, int K, int lm_mode) {
+void run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}) {
   const Dims& dm = s->dm;
   ssd_model* m = s->m;
   hipStream_t st = s->stream;
@@ -729,9 +759,12 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
   // passes of few rows keep their activations as operand tiles (the persistent
   // pass stages rows)
   const int mt = M <= 16 ? 1 : 2;
-  const bool persistent = dm.bf16 && s->fw.on && M <= FWD_MAX_M && m->fwd_grid[mt - 1] > 0;
+  const bool persistent = pass_is_persistent(s, M);
   const int tiled = dm.bf16 && M <= ROWS_MAX && !persistent;
-  embed(dm, m->emb, s->tok, M, m->layers[0].g1, s->x, s->xn, s->xn_plane, tiled, s->ssq, st);
+  const TokIn tok = io.tok ? TokIn{io.tok, K, io.tok_stride, io.tok_rows} : TokIn{s->tok, K, K, B};
+  float* const logits = io.logits ? io.logits : s->logits;
+  float* const x_last = io.h_pre ? io.h_pre : s->x;  // the last layer's residual
+  embed(dm, m->emb, tok, io.zero, io.n_zero, M, m->layers[0].g1, s->x, s->xn, s->xn_plane, tiled, s->ssq, st);
   int ssq_parts = 1;
 
   EpiArgs base{};
@@ -749,6 +782,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
   base.qrows_pad = q_rows_pad(K, dm.Hq / dm.Hkv);
   base.rope = s->rope;
   base.x = s->x;
+  base.xo = s->x;
   base.xn = s->xn;
   base.ssq_out = s->ssq;
   base.ssq_out_ld = s->ssq_rows_ld;
@@ -867,6 +901,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.kind = EPI_RESID;
       e.ssq = nullptr;
       e.gnext = (l + 1 < dm.L) ? m->layers[l + 1].g1 : m->gf;
+      if (l + 1 == dm.L) e.xo = x_last;
       e.ld = d;
       m->prof.run(3, dn_bytes, st, [&] {
         gemm_bf16(p2, W.w2, d, dm.dff, in_h, M, e, s->gpart, s->gcnt, st);
@@ -877,7 +912,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
     e.kind = EPI_LOGITS;
     e.ssq = s->ssq;
     e.ssq_parts = ssq_parts;
-    e.logits = s->logits;
+    e.logits = logits;
     e.ld = dm.Vimg;
     if (lm_mode == 0) {
       GemmPlan pl = gemm_plan_bf16(M, dm.Vimg, d, X);
@@ -930,6 +965,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
       e.kind = EPI_RESID;
       e.ssq = nullptr;
       e.gnext = (l + 1 < dm.L) ? m->layers[l + 1].g1 : m->gf;
+      if (l + 1 == dm.L) e.xo = x_last;
       e.ld = d;
       ssq_parts = gemm_f32((const float*)W.w2, d, dm.dff, (const float*)s->h, dm.dff, M, e, st);
     }
@@ -937,7 +973,7 @@ void run_forward(ssd_session* s, int K, int lm_mode) {
     e.kind = EPI_LOGITS;
     e.ssq = s->ssq;
     e.ssq_parts = ssq_parts;
-    e.logits = s->logits;
+    e.logits = logits;
     e.ld = dm.Vimg;
     if (lm_mode == 0) {
       gemm_f32((const float*)m->wlm, dm.Vimg, d, (const float*)s->xn, d, M, e, st);
@@ -1055,6 +1091,12 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
     const size_t qcap = (size_t)B * dm.Hkv * q_rows_pad(std::max(P, Kmax), dm.Hq / dm.Hkv) * dm.D;
     auto layout = [&](Arena& mem) {
       s->d_f = mem.get<int>(B);
+      s->ref_flag = mem.get<int>((size_t)B * s->ring);
+      s->gcnt_cap = gcnt;
+      s->gcnt = mem.get<unsigned>(gcnt);
+      s->acnt_cap = acnt;
+      s->acnt = mem.get<unsigned>(acnt);
+      s->zeroed_end = mem.get<char>(0);
       s->tok = mem.get<int>(M);
       s->acc = mem.get<unsigned char>(M);
       s->cnt = mem.get<int>((size_t)NCNT_ROUNDS * B);  // [round of the block][B] in image decodes
@@ -1076,19 +1118,14 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
       s->carry = mem.get<float>((size_t)B * dm.Vimg);
       s->ref = mem.get<float>((size_t)B * s->ring * dm.Vimg);
       s->refstage = mem.get<float>((size_t)B * Kmax * dm.Vimg);
-      s->ref_flag = mem.get<int>((size_t)B * s->ring);
       s->kv_layer_elems = (size_t)B * dm.Hkv * s->Lmax * dm.D;
       s->kc = mem.get<char>(s->kv_layer_elems * dm.L * es);
       s->vc = mem.get<char>(s->kv_layer_elems * dm.L * es);
       s->rope = mem.get<float2>((size_t)s->Lmax * (dm.D / 2));
       s->gpart_cap = gpart;
       s->gpart = mem.get<float>(gpart);
-      s->gcnt_cap = gcnt;
-      s->gcnt = mem.get<unsigned>(gcnt);
       s->apart_cap = apart;
       s->apart = mem.get<float>(apart);
-      s->acnt_cap = acnt;
-      s->acnt = mem.get<unsigned>(acnt);
     };
     Arena measure;
     layout(measure);
@@ -1140,14 +1177,11 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
       fill_u32(fw.flags, fw.n_flags, 0u, st);
       fw.on = true;
     }
-    // zero state that kernels read before writing (KV slots beyond the context are multiplied by 0)
-    fill_u32((unsigned*)s->kc, s->kv_layer_elems * dm.L * es / 4, 0u, st);
+    // zero state that kernels read before writing (value slots beyond the context are multiplied by 0)
+    // (a key slot past the context only makes a score that the mask replaces)
     fill_u32((unsigned*)s->vc, s->kv_layer_elems * dm.L * es / 4, 0u, st);
-    fill_u32((unsigned*)s->ref_flag, (size_t)B * s->ring, 0u, st);
     fill_u32((unsigned*)s->q, qcap, 0u, st);  // padded query rows are read (and masked) by attention
-    fill_u32(s->gcnt, gcnt, 0u, st);
-    fill_u32(s->acnt, acnt, 0u, st);
-    fill_u32((unsigned*)s->d_f, B, 0u, st);
+    fill_u32((unsigned*)s->d_f, (size_t)(s->zeroed_end - (char*)s->d_f) / 4, 0u, st);  // frontiers, flags, counters
     rope_table(s->rope, s->Lmax, dm.D / 2, (double)dm.theta, st);
     HIPCHK(hipGetLastError());
   } catch (HipError& e) {
@@ -1416,12 +1450,13 @@ namespace {
 
 // Enqueue one head on R rows of workspace w: hin [R][d] fp32 pre-norm states
 // and tok [R] vocabulary ids (device).  Leaves the drafts (absolute image-code
-// ids, lowest id among equal maxima) in w.out and the draft logits in w.logits.
-void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin, const int* tok, hipStream_t st) {
+// ids, lowest id among equal maxima) in out and the draft logits in logits
+// (device arrays; the states and logits 16-byte aligned).
+void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin, const int* tok, int* out, float* logits,
+                  hipStream_t st) {
   ssd_model* m = h->m;
   const Dims& dm = m->dm;
   const int d = h->d, mi = h->mi;
-  fill_u32((unsigned*)w.x, (size_t)R * d, 0u, st);  // u accumulates onto zero
   EpiArgs base{};
   base.Kblk = w.rows;  // every row is block position t of "sequence" 0
   base.f = w.f0;
@@ -1433,18 +1468,20 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
   base.Hkv = dm.Hkv;
   base.D = dm.D;
   base.x = w.x;
+  base.xo = w.x;
   base.xn = w.xn;
   base.xn_plane = w.xn_plane;
   base.ssq_out = w.ssq;
   base.ssq_out_ld = w.rows;
   base.h = w.hb;
   base.h_plane = w.hb_plane;
-  base.logits = w.logits;
+  base.logits = logits;
   if (!dm.bf16) {
     // fp32 models: plain fp32 GEMMs
     draft_input_f32(hin, (const float*)m->emb, tok, R, d, (float*)w.z, st);
     EpiArgs e = base;
     e.kind = EPI_RESID;  // u = W0 [h; e]; n = g * u
+    e.x = nullptr;
     e.gnext = h->g;
     e.ld = d;
     int parts = gemm_f32((const float*)h->w0, d, 2 * d, (const float*)w.z, 2 * d, R, e, st);
@@ -1483,6 +1520,7 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     GemmPlan p0 = plan(d, 2 * d);
     EpiArgs e = base;
     e.kind = EPI_RESID;
+    e.x = nullptr;
     e.gnext = h->g;
     e.ld = d;
     gemm_bf16(p0, h->w0, d, 2 * d, rows_of(w.z, w.z_plane, 2 * d), R, e, w.gpart, w.gcnt, st);
@@ -1510,7 +1548,7 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     e.ld = dm.Vimg;
     gemm_bf16(p3, m->wlm, dm.Vimg, d, rows_of(w.xn, w.xn_plane, d), R, e, w.gpart, w.gcnt, st);
   }
-  first_token(R, dm.Vimg, dm.img_lo, w.logits, SSD_GREEDY, 0, 1.0, 0, nullptr, w.out, 1, st);
+  first_token(R, dm.Vimg, dm.img_lo, logits, SSD_GREEDY, 0, 1.0, 0, nullptr, out, 1, st);
   HIPCHK(hipGetLastError());
 }
 
@@ -1668,11 +1706,16 @@ ssd_status ssd_draft_head_run(ssd_draft_head* h, int32_t R, const float* hs, con
   hipStream_t st = m->stream;
   try {
     const HeadWork& w = h->work;
-    HIPCHK(hipMemcpyAsync(w.hin, hs, (size_t)R * d * 4, hipMemcpyDefault, st));
-    HIPCHK(hipMemcpyAsync(w.tok, tokens, (size_t)R * 4, hipMemcpyDefault, st));
-    head_forward(h, w, R, w.hin, w.tok, st);
-    HIPCHK(hipMemcpyAsync(drafts, w.out, (size_t)R * 4, hipMemcpyDefault, st));
-    if (logits_out) HIPCHK(hipMemcpyAsync(logits_out, w.logits, (size_t)R * dm.Vimg * 4, hipMemcpyDefault, st));
+    // arrays in this GPU's memory are read and written in place, the others staged
+    const bool h_local = is_local_ptr(hs, 16), t_local = is_local_ptr(tokens, 4), d_local = is_local_ptr(drafts, 4),
+               l_local = is_local_ptr(logits_out, 16);
+    if (!h_local) HIPCHK(hipMemcpyAsync(w.hin, hs, (size_t)R * d * 4, hipMemcpyDefault, st));
+    if (!t_local) HIPCHK(hipMemcpyAsync(w.tok, tokens, (size_t)R * 4, hipMemcpyDefault, st));
+    head_forward(h, w, R, h_local ? hs : w.hin, t_local ? tokens : w.tok, d_local ? drafts : w.out,
+                 l_local ? logits_out : w.logits, st);
+    if (!d_local) HIPCHK(hipMemcpyAsync(drafts, w.out, (size_t)R * 4, hipMemcpyDefault, st));
+    if (logits_out && !l_local)
+      HIPCHK(hipMemcpyAsync(logits_out, w.logits, (size_t)R * dm.Vimg * 4, hipMemcpyDefault, st));
     if (host_out) HIPCHK(hipStreamSynchronize(st));
   } catch (HipError& e) {
     h->poisoned = true;
@@ -1753,11 +1796,15 @@ ssd_status ssd_draft_head_run_noalloc(ssd_draft_head* h, int32_t R, const float*
     // the array keeps the last call's contents: counters and the block-start lookup start at zero
     fill_u32(w.gcnt, gcnt, 0u, st);
     fill_u32((unsigned*)w.f0, 1, 0u, st);
-    HIPCHK(hipMemcpyAsync(w.hin, hs, r * d * 4, hipMemcpyDeviceToDevice, st));
-    HIPCHK(hipMemcpyAsync(w.tok, tokens, r * 4, hipMemcpyDeviceToDevice, st));
-    head_forward(h, w, R, w.hin, w.tok, st);
-    HIPCHK(hipMemcpyAsync(drafts, w.out, r * 4, hipMemcpyDeviceToDevice, st));
-    if (logits_out) HIPCHK(hipMemcpyAsync(logits_out, w.logits, r * dm.Vimg * 4, hipMemcpyDeviceToDevice, st));
+    const bool h_local = is_local_ptr(hs, 16), t_local = is_local_ptr(tokens, 4), d_local = is_local_ptr(drafts, 4),
+               l_local = is_local_ptr(logits_out, 16);
+    if (!h_local) HIPCHK(hipMemcpyAsync(w.hin, hs, r * d * 4, hipMemcpyDeviceToDevice, st));
+    if (!t_local) HIPCHK(hipMemcpyAsync(w.tok, tokens, r * 4, hipMemcpyDeviceToDevice, st));
+    head_forward(h, w, R, h_local ? hs : w.hin, t_local ? tokens : w.tok, d_local ? drafts : w.out,
+                 l_local ? logits_out : w.logits, st);
+    if (!d_local) HIPCHK(hipMemcpyAsync(drafts, w.out, r * 4, hipMemcpyDeviceToDevice, st));
+    if (logits_out && !l_local)
+      HIPCHK(hipMemcpyAsync(logits_out, w.logits, r * dm.Vimg * 4, hipMemcpyDeviceToDevice, st));
   } catch (HipError& e) {
     h->poisoned = true;
     return fail(SSD_E_DEVICE, "%s: %s", e.what, hipGetErrorString(e.e));
@@ -1876,33 +1923,52 @@ ssd_status ssd_verify_step(ssd_session* s, int32_t K, int32_t* tokens, const flo
                         (accept_count && !is_device_ptr(accept_count)) || (frontier && !is_device_ptr(frontier)) ||
                         (logits_out && !is_device_ptr(logits_out)) || (h_pre_out && !is_device_ptr(h_pre_out));
   hipStream_t st = s->stream;
+  // arrays in this GPU's memory are read and written in place; the others are
+  // staged through the session's
+  const bool tok_local = is_local_ptr(tokens, 4), acc_local = is_local_ptr(accept_mask, 1),
+             cnt_local = is_local_ptr(accept_count, 4), log_local = is_local_ptr(logits_out, 16),
+             h_local = is_local_ptr(h_pre_out, 16) && !s->cfg && !pass_is_persistent(s, B * K),
+             ref_local = is_local_ptr(ref_logits, 4);
   try {
-    HIPCHK(hipMemcpyAsync(s->tok, tokens, (size_t)nb * K * 4, hipMemcpyDefault, st));
-    // a guided image's block goes to both of its streams
-    if (s->cfg) HIPCHK(hipMemcpyAsync(s->tok + (size_t)nb * K, s->tok, (size_t)nb * K * 4, hipMemcpyDeviceToDevice, st));
-    if (ref_logits && !prm->commit)
-    {
-      // the caller's array may be host memory: stage it on the device first
-      HIPCHK(hipMemcpyAsync(s->refstage, ref_logits, (size_t)nb * K * dm.Vimg * 4, hipMemcpyDefault, st));
-      set_ref_rows(nb, K, K, dm.Vimg, s->refstage, s->d_f, s->ref, s->ref_flag, s->ring, 0, st);
+    int* const tok = tok_local ? tokens : s->tok;
+    int* const cnt = cnt_local && !prm->commit ? accept_count : s->cnt;
+    if (!tok_local) HIPCHK(hipMemcpyAsync(s->tok, tokens, (size_t)nb * K * 4, hipMemcpyDefault, st));
+    if (ref_logits && !prm->commit) {
+      const float* src = ref_logits;
+      if (!ref_local) {
+        HIPCHK(hipMemcpyAsync(s->refstage, ref_logits, (size_t)nb * K * dm.Vimg * 4, hipMemcpyDefault, st));
+        src = s->refstage;
+      }
+      set_ref_rows(nb, K, K, dm.Vimg, src, s->d_f, s->ref, s->ref_flag, s->ring, 0, st);
     }
     const bool all_rows = !prm->commit || logits_out;
-    run_forward(s, K, all_rows ? 0 : 1);
+    PassIo io;
+    io.tok = tok;
+    io.tok_stride = K;
+    io.tok_rows = nb;  // a guided image's block goes to both of its streams
+    io.zero = prm->commit ? nullptr : cnt;
+    io.n_zero = prm->commit ? 0 : nb;
+    io.h_pre = h_local ? h_pre_out : nullptr;
+    if (log_local && !s->cfg && !pass_is_persistent(s, B * K)) io.logits = logits_out;
+    run_forward(s, K, all_rows ? 0 : 1, io);
     // per-image scores: the pass's own logits, or the guided mix of the two streams
-    const float* lg = s->logits;
+    const float* lg = io.logits ? io.logits : s->logits;
+    const float* own = lg;
     const float* cy = s->carry;
     if (s->cfg && all_rows) {
-      cfg_mix(nb, K, dm.Vimg, s->cfg_w, s->logits, s->carry, s->mlog, s->mcarry, st);
-      lg = s->mlog;
+      float* mix = log_local ? logits_out : s->mlog;
+      cfg_mix(nb, K, dm.Vimg, s->cfg_w, s->logits, s->carry, mix, s->mcarry, st);
+      lg = mix;
       cy = s->mcarry;
     }
-    if (logits_out) HIPCHK(hipMemcpyAsync(logits_out, lg, (size_t)nb * K * dm.Vimg * 4, hipMemcpyDefault, st));
-    if (h_pre_out) HIPCHK(hipMemcpyAsync(h_pre_out, s->x, (size_t)nb * K * dm.d * 4, hipMemcpyDefault, st));
+    if (logits_out && lg != logits_out)
+      HIPCHK(hipMemcpyAsync(logits_out, lg, (size_t)nb * K * dm.Vimg * 4, hipMemcpyDefault, st));
+    if (h_pre_out && !h_local)
+      HIPCHK(hipMemcpyAsync(h_pre_out, s->x, (size_t)nb * K * dm.d * 4, hipMemcpyDefault, st));
     if (prm->commit) {
-      commit_update(B, all_rows ? K : -K, dm.Vimg, s->logits, s->carry, s->d_f, s->ref_flag, s->ring, st);
+      commit_update(B, all_rows ? K : -K, dm.Vimg, own, s->carry, s->d_f, s->ref_flag, s->ring, st);
       for (int b = 0; b < B; ++b) s->f[b] += K;
     } else {
-      fill_u32((unsigned*)s->cnt, nb, 0u, st);
       SelectArgs a{};
       a.rule = prm->rule;
       a.top_k = prm->top_k;
@@ -1916,21 +1982,24 @@ ssd_status ssd_verify_step(ssd_session* s, int32_t K, int32_t* tokens, const flo
       a.img_lo = dm.img_lo;
       a.truncate = prm->truncate;
       a.f = s->d_f;
-      a.tokens = s->tok;
+      a.tokens = tok;
+      a.tok_stride = K;
       a.logits = lg;
       a.carry = cy;
       a.ref = s->ref;
       a.ref_flag = s->ref_flag;
       a.ring = s->ring;
-      a.accept = s->acc;
-      a.count = s->cnt;
+      a.accept = acc_local ? accept_mask : s->acc;
+      a.count = cnt;
       a.amax = s->amax;
       select_tokens(a, st);
       if (prm->truncate) truncate_finalize(a, s->d_f, st);
       HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpyAsync(tokens, s->tok, (size_t)nb * K * 4, hipMemcpyDefault, st));
-      if (accept_mask) HIPCHK(hipMemcpyAsync(accept_mask, s->acc, (size_t)nb * K, hipMemcpyDefault, st));
-      if (accept_count) HIPCHK(hipMemcpyAsync(accept_count, s->cnt, (size_t)nb * 4, hipMemcpyDefault, st));
+      if (!tok_local) HIPCHK(hipMemcpyAsync(tokens, s->tok, (size_t)nb * K * 4, hipMemcpyDefault, st));
+      if (accept_mask && !acc_local)
+        HIPCHK(hipMemcpyAsync(accept_mask, s->acc, (size_t)nb * K, hipMemcpyDefault, st));
+      if (accept_count && !cnt_local)
+        HIPCHK(hipMemcpyAsync(accept_count, s->cnt, (size_t)nb * 4, hipMemcpyDefault, st));
       if (prm->truncate) {
         HIPCHK(hipMemcpyAsync(s->f.data(), s->d_f, (size_t)B * 4, hipMemcpyDeviceToHost, st));
         fwd_abort_fetch(s);
@@ -2222,7 +2291,7 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
     a.Vimg = dm.Vimg;
     a.img_lo = dm.img_lo;
     a.f = s->d_f;
-    a.tokens = s->tok;
+    a.tokens = s->tok;  // (strict decode: blocks gathered at each frontier)
     a.logits = lg;
     a.carry = cy;
     a.ref = s->ref;
@@ -2305,6 +2374,7 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
         gather_block(s->img, NS, s->d_f, P, Kp, B, s->tok, st);
         run_forward(s, Kp, 0);
         a.K = Kp;
+        a.tok_stride = Kp;
         a.n_fixed = 1;
         a.round = 0;
         a.truncate = 1;
@@ -2415,7 +2485,7 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
                                 hipMemcpyDeviceToDevice, st));
         for (int j = 1; j <= o.K; ++j) {
           ssd_draft_head* h = (hor ? src.hh : src.vh)[j - 1];
-          head_forward(h, h->work, B * n_src, s->hsrc, s->tsrc, st);
+          head_forward(h, h->work, B * n_src, s->hsrc, s->tsrc, h->work.out, h->work.logits, st);
           const int dq = seq_of(p0 + j * step);  // a run or a row: contiguous in the sequence
           HIPCHK(hipMemcpy2DAsync(s->img + dq, (size_t)NS * 4, h->work.out, (size_t)n_src * 4, (size_t)n_src * 4, B,
                                   hipMemcpyDeviceToDevice, st));
@@ -2433,10 +2503,10 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
       // the pass's block: this op's, behind the pending commit's when there is one
       const int Kc = (o.kind == 0 && pending) ? pending->K : 0;
       const int start = o.start - Kc, K = o.K + Kc;
-      HIPCHK(hipMemcpy2DAsync(s->tok, (size_t)K * 4, s->img + start, (size_t)NS * 4, (size_t)K * 4, B,
-                              hipMemcpyDeviceToDevice, st));
-      if (s->cfg)
-        HIPCHK(hipMemcpyAsync(s->tok + (size_t)B * K, s->tok, (size_t)B * K * 4, hipMemcpyDeviceToDevice, st));
+      PassIo io;  // the block is read, and corrected, in the working grid
+      io.tok = s->img + start;
+      io.tok_stride = NS;
+      io.tok_rows = B;
       if (o.kind == 0) {
         if (use_q) {
           // first round of a position: its reference is its draft distribution
@@ -2445,16 +2515,16 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
           set_ref_rows(B, K, NS, dm.Vimg, s->qtab + (size_t)start * dm.Vimg, s->d_f, s->ref, s->ref_flag, s->ring,
                        1, st);
         }
-        run_forward(s, K, 0);
+        run_forward(s, K, 0, io);
         if (s->cfg) cfg_mix(B, K, dm.Vimg, s->cfg_w, s->logits, s->carry, s->mlog, s->mcarry, st);
         const int rr = std::min(o.rib, NCNT_ROUNDS - 1);
         a.K = K;
+        a.tokens = s->img + start;
+        a.tok_stride = NS;
         a.n_fixed = Kc + o.nf;  // the committed prefix is fixed
         a.round = (unsigned)o.rnd;
         a.count = s->cnt + (size_t)rr * Bs;
         select_tokens(a, st);
-        HIPCHK(hipMemcpy2DAsync(s->img + start, (size_t)NS * 4, s->tok, (size_t)K * 4, (size_t)K * 4, B,
-                                hipMemcpyDeviceToDevice, st));
         ++nv;
         int n_eol = 0;  // end-of-line slots are not verified
         for (int k = 0; eol && k < o.K; ++k) n_eol += (o.start + k) % RW == W;
@@ -2468,7 +2538,7 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
           pending = nullptr;
         }
       } else {
-        run_forward(s, o.K, 1);
+        run_forward(s, o.K, 1, io);
         commit_update(Bs, -o.K, dm.Vimg, s->logits, s->carry, s->d_f, s->ref_flag, s->ring, st);
         for (int b = 0; b < Bs; ++b) s->f[b] += o.K;
         keep_states(o.start, o.K, o.K);

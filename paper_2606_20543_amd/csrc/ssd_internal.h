@@ -67,8 +67,9 @@ struct EpiArgs {
   int Lmax, Hq, Hkv, D;
   int qrows_pad;         // q_rows_pad(Kblk, Hq / Hkv): rows per KV head of the tiled q (bf16 models)
   const float2* rope;    // [Lmax][D/2] (cos, sin)
-  // EPI_RESID: x += v; xn = bf16(gnext * x); ssq_out[fb][t] = sum over the block's features of x^2
-  float* x;
+  // EPI_RESID: xo = x + v; xn = bf16(gnext * xo); ssq_out[fb][t] = sum over the block's features of xo^2
+  const float* x;        // nullptr: zero
+  float* xo;             // the new residual (x itself, or the caller's array in the last layer)
   void* xn;
   const float* gnext;
   float* ssq_out;
@@ -256,8 +257,15 @@ inline int f32_feature_blocks(int N) { return (N + 15) / 16; }
 void pack_bf16_tiles(const uint16_t* src, const int* rowmap, int N, int K, void* dst, hipStream_t st);
 void gather_rows_f32(const float* src, const int* rowmap, int N, int K, float* dst, hipStream_t st);
 
-// x[t] = E[tok[t]]; xn = g * x (split planes for bf16 models, laid out by act_index); ssq[t] = sum x^2 (one part)
-void embed(const Dims& dm, const void* emb, const int* tok, int M, const float* g, float* x, void* xn,
+// Tokens of a pass: row t is block position t % K of sequence b = t / K, its id at
+// ids[(b % rows) * stride + t % K] (guided passes feed an image's block to both of its streams).
+struct TokIn {
+  const int* ids;
+  int K, stride, rows;
+};
+// x[t] = E[token of t]; xn = g * x (split planes for bf16 models, laid out by act_index); ssq[t] = sum x^2
+// (one part); zero[0 .. n_zero) = 0 (counters of the pass)
+void embed(const Dims& dm, const void* emb, const TokIn& tok, int* zero, int n_zero, int M, const float* g, float* x, void* xn,
            size_t xn_plane, int tiled, float* ssq, hipStream_t st);
 // fp32 path: ssq[t] = sum x^2 of row t (one part)
 void norm_rows_f32(const float* x, int M, int d, float* ssq, hipStream_t st);
@@ -371,7 +379,8 @@ struct SelectArgs {
   int n_fixed, K, B, Vimg, img_lo;
   int truncate;
   const int* f;
-  int* tokens;             // [B][K] absolute ids (in/out)
+  int* tokens;             // [B][tok_stride] absolute ids of the block (in/out)
+  int tok_stride;
   const float* logits;     // [B*K][Vimg]
   const float* carry;      // [B][Vimg]
   float* ref;              // ring [B][ring][Vimg]

@@ -432,7 +432,10 @@ __device__ __forceinline__ void epi_load(const EpiArgs& e, int nb0, int N, int M
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int tl = mt * 16 + (lane & 15);
-        op.a[nt][mt] = Mem::ldf4(e.x, ((size_t)(t0 + (tl < M ? tl : M - 1)) * e.ld + n) * 4);
+        // without an old residual the load reads g_next and is ignored (no branch around it)
+        const size_t i = (size_t)(t0 + (tl < M ? tl : M - 1)) * e.ld + n;
+        const float4 v = Mem::ldf4(e.x ? e.x : e.gnext, (e.x ? i : (size_t)n) * 4);
+        op.a[nt][mt] = e.x ? v : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
   } else if (e.kind == EPI_QKV) {
@@ -521,7 +524,7 @@ __device__ __forceinline__ void epi_store(const EpiArgs& e, const floatx4 (&acc)
           const float4 xo = op.a[nt][mt];
           const float4 g = op.g[nt];
           const float4 xv = make_float4(xo.x + v[0], xo.y + v[1], xo.z + v[2], xo.w + v[3]);
-          Mem::stf4(e.x, i * 4, xv);
+          Mem::stf4(e.xo, i * 4, xv);
           uint32_t h0, l0, h1, l1;
           split2(g.x * xv.x, g.y * xv.y, h0, l0);
           split2(g.z * xv.z, g.w * xv.w, h1, l1);
