@@ -123,6 +123,16 @@ void embed(const Dims& dm, const void* emb, const TokIn& tok, int* zero, int n_z
                        x, (float*)xn, ssq);
 }
 
+// one 16-byte piece a thread: at most a few rows, a launch's latency
+__global__ __launch_bounds__(256) void last_rows_kernel(const float* x, int K, int d, float* out) {
+  const int c = (blockIdx.x * 256 + threadIdx.x) * 4, b = blockIdx.y;
+  if (c < d) *(float4*)(out + (size_t)b * d + c) = *(const float4*)(x + ((size_t)b * K + K - 1) * d + c);
+}
+
+void last_rows(const float* x, int B, int K, int d, float* out, hipStream_t st) {
+  hipLaunchKernelGGL(last_rows_kernel, dim3((d + 1023) / 1024, B), dim3(256), 0, st, x, K, d, out);
+}
+
 __global__ __launch_bounds__(256) void ssq_kernel(const float* x, int d, float* ssq) {
   __shared__ float red[256];
   const int t = blockIdx.x;

@@ -737,6 +737,7 @@ struct PassIo {
   float* h_pre = nullptr;    // [M][d] (kernel-per-projection passes only)
   int* zero = nullptr;       // cleared by the pass's first kernel
   int n_zero = 0;
+  bool last_state = false;   // no caller reads the final states of other rows than each sequence's last
 };
 
 // a pass whose projections and attention run as one launch
@@ -744,8 +745,61 @@ bool pass_is_persistent(const ssd_session* s, int M) {
   return s->dm.bf16 && s->fw.on && M <= FWD_MAX_M && s->m->fwd_grid[M <= 16 ? 0 : 1] > 0;
 }
 
-// lm_mode: 0 = logits for all B*K rows; 1 = logits for the last row of each sequence only
-void run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}) {
+// The last layer behind its attention for the last row of each sequence only
+// (base: the pass's epilogue arguments; in_o: the attention output of all rows).
+// Leaves the rows' final states in s->x [B][d] and the output layer's inputs in
+// s->xn and s->ssq; returns the count of x^2 parts.
+int last_layer_tail(ssd_session* s, int K, EpiArgs base, ActIn in_o, hipStream_t st) {
+  const Dims& dm = s->dm;
+  ssd_model* m = s->m;
+  const int B = s->B, d = dm.d, qd = dm.Hq * dm.D, dff = dm.dff, X = m->xcd;
+  const double A = 4.0, es = (double)esize(dm);
+  const LayerW& W = m->layers[dm.L - 1];
+  const GemmPlan po = gemm_plan_bf16(B, d, qd, X), p13 = gemm_plan_bf16(B, 2 * dff, d, X), p2 = gemm_plan_bf16(B, d, dff, X);
+  for (const GemmPlan* gp : {&po, &p13, &p2})
+    if (gemm_partials_floats(*gp, B) > s->gpart_cap || (size_t)gemm_counters(*gp) > s->gcnt_cap)
+      throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
+  if (gemm_parts(po, d) > s->ssq_parts_cap || gemm_parts(p2, d) > s->ssq_parts_cap)
+    throw HipError{hipErrorInvalidValue, "rms partial sums exceed their buffer"};
+  base.tiled = B <= ROWS_MAX;
+  const ActIn in_x{(const uint16_t*)s->xn, s->xn_plane, d, 0, 1, base.tiled},
+      in_h{(const uint16_t*)s->h, s->h_plane, dff, 0, 1, base.tiled};
+  float* const xl = (float*)s->h;
+  last_rows(s->x, B, K, d, xl, st);
+  in_o.row0 = K - 1;
+  in_o.rstep = K;
+  EpiArgs e = base;
+  e.kind = EPI_RESID;
+  e.ssq = nullptr;
+  e.x = xl;
+  e.gnext = W.g2;
+  e.ld = d;
+  m->prof.run(1, (double)d * qd * es + (double)B * qd * A + (double)B * d * (8 + A), st, [&] {
+    gemm_bf16(po, W.wo, d, qd, in_o, B, e, s->gpart, s->gcnt, st);
+  }, 2.0 * B * d * qd, po.tile);
+  e = base;
+  e.kind = EPI_SWIGLU;
+  e.ssq = s->ssq;
+  e.ssq_parts = gemm_parts(po, d);
+  e.h = s->h;
+  e.ld = dff;
+  m->prof.run(2, 2.0 * dff * d * es + (double)B * d * A + (double)B * dff * A, st, [&] {
+    gemm_bf16(p13, W.w13, 2 * dff, d, in_x, B, e, s->gpart, s->gcnt, st);
+  }, 2.0 * B * 2 * dff * d, p13.tile);
+  e = base;
+  e.kind = EPI_RESID;
+  e.ssq = nullptr;
+  e.gnext = m->gf;
+  e.ld = d;
+  m->prof.run(3, (double)d * dff * es + (double)B * dff * A + (double)B * d * (8 + A), st, [&] {
+    gemm_bf16(p2, W.w2, d, dff, in_h, B, e, s->gpart, s->gcnt, st);
+  }, 2.0 * B * d * dff, p2.tile);
+  return gemm_parts(p2, d);
+}
+
+// lm_mode: 0 = logits for all B*K rows; 1 = logits for the last row of each sequence only.
+// Returns true if s->x then holds the final states of those last rows alone, [B][d], else false ([B*K][d]).
+bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}) {
   const Dims& dm = s->dm;
   ssd_model* m = s->m;
   hipStream_t st = s->stream;
@@ -854,13 +908,23 @@ void run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       const double fwd_bytes = dm.L * (qkv_bytes + attn_bytes + o_bytes + gu_bytes + dn_bytes) + lm_bytes;
       m->prof.run(6, fwd_bytes, st, [&] { HIPCHK(fwd_persistent(a, mt, D, G, st)); });
       HIPCHK(hipGetLastError());
-      return;
+      return false;
     }
     auto rows_of = [&](const void* p, size_t plane, int ld) {
       return ActIn{(const uint16_t*)p, plane, ld, 0, 1, tiled};
     };
     const ActIn in_x = rows_of(s->xn, s->xn_plane, d), in_o = rows_of(s->o, s->o_plane, dm.Hq * D),
                 in_h = rows_of(s->h, s->h_plane, dm.dff);
+    // Where only each sequence's last row is asked for, nothing reads what the
+    // other rows become behind the last layer's attention (their keys and
+    // values are cached by then): that layer's O, gate/up and down projections
+    // run on the B last rows, gathered to the front of the arrays (the h array,
+    // free until gate/up writes it, holds their residuals meanwhile).  Worth the
+    // gather's launch where it saves 16-row tiles, the step of the GEMMs' cost.
+    // ssd_prefill to free of eight 256-token prompts, 8B widths, two layers:
+    // 3155 -> 1999 us; of one 64-token prompt, 24 layers of the 1B widths: 1784 -> 1775.
+    const bool compact = lm_mode == 1 && io.last_state && (M + 15) / 16 > (B + 15) / 16 &&
+                         (size_t)B * d * 4 <= s->h_plane * 4;
     for (int l = 0; l < dm.L; ++l) {
       const LayerW& W = m->layers[l];
       char* kc = (char*)s->kc + (size_t)l * s->kv_layer_elems * es;
@@ -879,6 +943,10 @@ void run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
         attention_bf16(dm, pa, B, K, s->d_f, s->q, s->q_plane, kc, vc, s->Lmax, s->o, s->o_plane, tiled, s->apart,
                        s->acnt, st);
       }, attn_flops);
+      if (compact && l + 1 == dm.L) {
+        ssq_parts = last_layer_tail(s, K, base, in_o, st);
+        continue;
+      }
       e = base;
       e.kind = EPI_RESID;
       e.ssq = nullptr;
@@ -922,17 +990,27 @@ void run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
         gemm_bf16(pl, m->wlm, dm.Vimg, d, in_x, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * dm.Vimg * d, pl.tile);
     } else {
-      e.ssq_off = K - 1;
-      e.ssq_step = K;
+      if (!compact) {
+        e.ssq_off = K - 1;
+        e.ssq_step = K;
+      }
       GemmPlan pl = gemm_plan_bf16(B, dm.Vimg, d, X);
       if (gemm_partials_floats(pl, B) > s->gpart_cap || (size_t)gemm_counters(pl) > s->gcnt_cap)
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
       m->prof.run(4, (double)dm.Vimg * d * es + (double)B * d * A + (double)B * dm.Vimg * 4, st, [&] {
         ActIn last = in_x;  // the last row of each sequence
-        last.row0 = K - 1;
-        last.rstep = K;
+        if (compact) {
+          last.tiled = B <= ROWS_MAX;
+        } else {
+          last.row0 = K - 1;
+          last.rstep = K;
+        }
         gemm_bf16(pl, m->wlm, dm.Vimg, d, last, B, e, s->gpart, s->gcnt, st);
       }, 2.0 * B * dm.Vimg * d, pl.tile);
+    }
+    if (compact) {
+      HIPCHK(hipGetLastError());
+      return true;
     }
   } else {
     for (int l = 0; l < dm.L; ++l) {
@@ -984,6 +1062,7 @@ void run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
     }
   }
   HIPCHK(hipGetLastError());
+  return false;
 }
 
 // Number of XCDs if workgroup w always runs on XCD w % X (checked on 4096
@@ -1195,10 +1274,14 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
 }
 
 // prefix pass: tokens already in s->tok as [B][P]
-void prefill_pass(ssd_session* s) {
-  run_forward(s, s->P, 1);
+// Returns what run_forward does: whether s->x holds the prompts' last states alone
+bool prefill_pass(ssd_session* s) {
+  PassIo io;
+  io.last_state = true;
+  const bool compact = run_forward(s, s->P, 1, io);
   commit_update(s->B, -s->P, s->dm.Vimg, s->logits, s->carry, s->d_f, s->ref_flag, s->ring, s->stream);
   for (int b = 0; b < s->B; ++b) s->f[b] = s->P;
+  return compact;
 }
 
 ssd_status check_tokens_host(const int32_t* t, size_t n, int lo, int hi, const char* what) {
@@ -1950,6 +2033,7 @@ ssd_status ssd_verify_step(ssd_session* s, int32_t K, int32_t* tokens, const flo
     io.n_zero = prm->commit ? 0 : nb;
     io.h_pre = h_local ? h_pre_out : nullptr;
     if (log_local && !s->cfg && !pass_is_persistent(s, B * K)) io.logits = logits_out;
+    io.last_state = !h_pre_out;
     run_forward(s, K, all_rows ? 0 : 1, io);
     // per-image scores: the pass's own logits, or the guided mix of the two streams
     const float* lg = io.logits ? io.logits : s->logits;
@@ -2271,12 +2355,12 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
     fill_u32((unsigned*)s->cnt, (size_t)NCNT_ROUNDS * Bs, 0u, st);
     for (int b = 0; b < Bs; ++b) s->f[b] = 0;
     HIPCHK(hipMemcpyAsync(s->tok, hpre.data(), hpre.size() * 4, hipMemcpyHostToDevice, st));
-    prefill_pass(s);
+    const bool last_alone = prefill_pass(s);
     ++passes;
     const size_t rowb = (size_t)dm.d * 4;  // bytes of one state
     if (heads)  // the state that scores image token 0: the prompt's last (conditional streams)
-      HIPCHK(hipMemcpy2DAsync(s->hs, (size_t)N * rowb, s->x + (size_t)(P - 1) * dm.d, (size_t)P * rowb, rowb, B,
-                              hipMemcpyDeviceToDevice, st));
+      HIPCHK(hipMemcpy2DAsync(s->hs, (size_t)N * rowb, last_alone ? s->x : s->x + (size_t)(P - 1) * dm.d,
+                              (last_alone ? 1 : (size_t)P) * rowb, rowb, B, hipMemcpyDeviceToDevice, st));
     // per-image scores: the streams' own logits, or their guided mix
     const float* lg = s->cfg ? s->mlog : s->logits;
     const float* cy = s->cfg ? s->mcarry : s->carry;
@@ -2444,7 +2528,9 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
       if (Kc > 0) {
         HIPCHK(hipMemcpy2DAsync(s->tok, (size_t)Kc * 4, s->img + x0, (size_t)NS * 4, (size_t)Kc * 4, B,
                                 hipMemcpyDeviceToDevice, st));
-        run_forward(s, Kc, 1);
+        PassIo last;
+        last.last_state = true;
+        run_forward(s, Kc, 1, last);
       }
       pa.logits = Kc > 0 ? s->logits : s->carry;
       pa.pos_off = Kc;
@@ -2538,6 +2624,7 @@ ssd_status decode_impl(ssd_model* m, const ssd_schedule* sc, int32_t B, int32_t 
           pending = nullptr;
         }
       } else {
+        io.last_state = !heads;  // keep_states reads every row's
         run_forward(s, o.K, 1, io);
         commit_update(Bs, -o.K, dm.Vimg, s->logits, s->carry, s->d_f, s->ref_flag, s->ring, st);
         for (int b = 0; b < Bs; ++b) s->f[b] += o.K;

@@ -267,6 +267,8 @@ struct TokIn {
 // (one part); zero[0 .. n_zero) = 0 (counters of the pass)
 void embed(const Dims& dm, const void* emb, const TokIn& tok, int* zero, int n_zero, int M, const float* g, float* x, void* xn,
            size_t xn_plane, int tiled, float* ssq, hipStream_t st);
+// out[b] = x[b K + K - 1], b < B (rows of d floats, a multiple of 4)
+void last_rows(const float* x, int B, int K, int d, float* out, hipStream_t st);
 // fp32 path: ssq[t] = sum x^2 of row t (one part)
 void norm_rows_f32(const float* x, int M, int d, float* ssq, hipStream_t st);
 
