@@ -641,7 +641,7 @@ def main():
                                    "the algorithmic 2*M*N*K", "timing": timing}
     else:
         gbs = s_by / (s_ms / 1e3) / 1e9 if s_ms > 0 else None
-        roofline = {"bound": "hbm", "kernel": "gemm_bf16_kernel + gemm_wide_kernel (weight streaming)",
+        roofline = {"bound": "hbm", "kernel": "gemm_rows_kernel (weight streaming)",
                     "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS if gbs else None,
                     "traffic": measured_traffic("stream", wl.name), "launches": s_n,
                     "ms_per_launch": s_ms / max(s_n, 1), "bytes_per_launch": s_by / max(s_n, 1), "timing": timing}

@@ -123,7 +123,8 @@ struct GemmKArgs {
   EpiArgs epi;
 };
 
-// Tiled GEMM for more than ROWS_MAX token rows (prefills, batches):
+// Tiled GEMM for more than ROWS_MAX token rows (prefills, batches), and for wide
+// projections of fewer (gemm_plan_bf16):
 // there the weights are worth reusing from registers and LDS rather than
 // streaming once per 64-row tile, and from a few hundred rows on the product
 // is bound by the matrix cores, not by the weight stream.  Each
@@ -711,7 +712,7 @@ __device__ __forceinline__ void t8_epilogue(const GemmKArgs& a, int fb, int ft, 
         const uint4 hi = *(const uint4*)(stg + row * 32 + c * 8);
         const uint4 lo = *(const uint4*)(stg + 2048 + row * 32 + c * 8);
         if (row < Mw && c < NT) {  // a wave's 8 NT outputs of a row are NT chunks
-          const size_t i = (size_t)(t0w + row) * e.ld + nb0 * 8 + c * 8;
+          const size_t i = act_index(e.tiled, t0w + row, nb0 * 8 + c * 8, e.ld);
           *(uint4*)(h + i) = hi;
           *(uint4*)(h + e.h_plane + i) = lo;
         }
@@ -761,7 +762,7 @@ __device__ __forceinline__ void t8_epilogue(const GemmKArgs& a, int fb, int ft, 
           const int row = k * 8 + (lane >> 3);
           const uint4 v = *(const uint4*)(stg + row * 64 + c * 8);
           if (row < Mw && c < 2 * NT)
-            *(uint4*)(xn + (pl ? e.xn_plane : 0) + (size_t)(t0w + row) * e.ld + nb0 * 16 + c * 8) = v;
+            *(uint4*)(xn + (pl ? e.xn_plane : 0) + act_index(e.tiled, t0w + row, nb0 * 16 + c * 8, e.ld)) = v;
         }
         asm volatile("" ::: "memory");  // the lo plane's writes stay behind the hi plane's reads
       }
@@ -949,9 +950,34 @@ static bool tile8_narrow_enabled() {
   return on;
 }
 
+static GemmPlan gemm_plan_tiles(int M, int N, int K, int xcd);
+
+GemmPlan gemm_plan_guided(int M, int N, int K, int xcd) {
+  return M <= 64 ? gemm_rows_plan(M, N, K, xcd) : gemm_plan_tiles(M, N, K, xcd);
+}
+
 GemmPlan gemm_plan_bf16(int M, int N, int K, int xcd) {
-  if (M <= ROWS_MAX) return gemm_rows_plan(M, N, K, xcd);
-  GemmPlan p;
+  if (M <= 64) return gemm_rows_plan(M, N, K, xcd);
+  if (M <= ROWS_MAX) {
+    // one 128-row tile: the few-row kernel with two row groups, or the 128 x 256
+    // tiles where their modelled time is less (8 us, 1.4 us a 64-input stage, whose
+    // weights come from HBM here, and 0.43 us a MB of partial sums out and back).
+    // At 128 rows of the 8B widths: gate/up 78 us on the tiles, 99 on the few-row
+    // kernel; output layer 87 and 101; but QKV 38 (64-feature tiles) and 31.5.  1B
+    // widths, on the 64-feature tiles and here: QKV 27.1 -> 19.6, O 16.1 -> 12, gate/up
+    // 33.3 -> 21.4, down 27.9 -> 18.1 us.
+    double ns;
+    const GemmPlan r = gemm_rows_plan(M, N, K, xcd, &ns);
+    const GemmPlan t = gemm_plan_tiles(M, N, K, xcd);
+    const double parts = t.S > 1 ? 8.0 * t.S * TILE_ROWS * N : 0.0;
+    if (t.tile == 3 && !t.tail_fb && 8e3 + 1400.0 * t.kchunks + 0.43e-3 * parts < ns) return t;
+    return r;
+  }
+  return gemm_plan_tiles(M, N, K, xcd);
+}
+
+static GemmPlan gemm_plan_tiles(int M, int N, int K, int xcd) {
+  GemmPlan p{};
   p.xcd = xcd;
   p.tile = 0;
   p.tail_fb = 0;

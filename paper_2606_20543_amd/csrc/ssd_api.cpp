@@ -745,25 +745,31 @@ bool pass_is_persistent(const ssd_session* s, int M) {
   return s->dm.bf16 && s->fw.on && M <= FWD_MAX_M && s->m->fwd_grid[M <= 16 ? 0 : 1] > 0;
 }
 
+GemmPlan pass_plan(const ssd_session* s, int M, int N, int K) {
+  return (s->cfg ? gemm_plan_guided : gemm_plan_bf16)(M, N, K, s->m->xcd);
+}
+// whether p's input is written as operand tiles (the 128 x 64 tiles, which run
+// guided passes from 65 rows on, write rows)
+int pass_tiled(const ssd_session* s, const GemmPlan& p, int M) { return plan_tiled(p, M) && !(s->cfg && M > 64); }
+
 // The last layer behind its attention for the last row of each sequence only
 // (base: the pass's epilogue arguments; in_o: the attention output of all rows).
 // Leaves the rows' final states in s->x [B][d] and the output layer's inputs in
 // s->xn and s->ssq; returns the count of x^2 parts.
-int last_layer_tail(ssd_session* s, int K, EpiArgs base, ActIn in_o, hipStream_t st) {
+int last_layer_tail(ssd_session* s, int K, const EpiArgs& base, ActIn in_o, int lm_tiled, hipStream_t st) {
   const Dims& dm = s->dm;
   ssd_model* m = s->m;
-  const int B = s->B, d = dm.d, qd = dm.Hq * dm.D, dff = dm.dff, X = m->xcd;
+  const int B = s->B, d = dm.d, qd = dm.Hq * dm.D, dff = dm.dff;
   const double A = 4.0, es = (double)esize(dm);
   const LayerW& W = m->layers[dm.L - 1];
-  const GemmPlan po = gemm_plan_bf16(B, d, qd, X), p13 = gemm_plan_bf16(B, 2 * dff, d, X), p2 = gemm_plan_bf16(B, d, dff, X);
+  const GemmPlan po = pass_plan(s, B, d, qd), p13 = pass_plan(s, B, 2 * dff, d), p2 = pass_plan(s, B, d, dff);
   for (const GemmPlan* gp : {&po, &p13, &p2})
     if (gemm_partials_floats(*gp, B) > s->gpart_cap || (size_t)gemm_counters(*gp) > s->gcnt_cap)
       throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
   if (gemm_parts(po, d) > s->ssq_parts_cap || gemm_parts(p2, d) > s->ssq_parts_cap)
     throw HipError{hipErrorInvalidValue, "rms partial sums exceed their buffer"};
-  base.tiled = B <= ROWS_MAX;
-  const ActIn in_x{(const uint16_t*)s->xn, s->xn_plane, d, 0, 1, base.tiled},
-      in_h{(const uint16_t*)s->h, s->h_plane, dff, 0, 1, base.tiled};
+  const ActIn in_x{(const uint16_t*)s->xn, s->xn_plane, d, 0, 1, pass_tiled(s, p13, B)},
+      in_h{(const uint16_t*)s->h, s->h_plane, dff, 0, 1, pass_tiled(s, p2, B)};
   float* const xl = (float*)s->h;
   last_rows(s->x, B, K, d, xl, st);
   in_o.row0 = K - 1;
@@ -773,6 +779,7 @@ int last_layer_tail(ssd_session* s, int K, EpiArgs base, ActIn in_o, hipStream_t
   e.ssq = nullptr;
   e.x = xl;
   e.gnext = W.g2;
+  e.tiled = in_x.tiled;
   e.ld = d;
   m->prof.run(1, (double)d * qd * es + (double)B * qd * A + (double)B * d * (8 + A), st, [&] {
     gemm_bf16(po, W.wo, d, qd, in_o, B, e, s->gpart, s->gcnt, st);
@@ -782,6 +789,7 @@ int last_layer_tail(ssd_session* s, int K, EpiArgs base, ActIn in_o, hipStream_t
   e.ssq = s->ssq;
   e.ssq_parts = gemm_parts(po, d);
   e.h = s->h;
+  e.tiled = in_h.tiled;
   e.ld = dff;
   m->prof.run(2, 2.0 * dff * d * es + (double)B * d * A + (double)B * dff * A, st, [&] {
     gemm_bf16(p13, W.w13, 2 * dff, d, in_x, B, e, s->gpart, s->gcnt, st);
@@ -790,6 +798,7 @@ int last_layer_tail(ssd_session* s, int K, EpiArgs base, ActIn in_o, hipStream_t
   e.kind = EPI_RESID;
   e.ssq = nullptr;
   e.gnext = m->gf;
+  e.tiled = lm_tiled;
   e.ld = d;
   m->prof.run(3, (double)d * dff * es + (double)B * dff * A + (double)B * d * (8 + A), st, [&] {
     gemm_bf16(p2, W.w2, d, dff, in_h, B, e, s->gpart, s->gcnt, st);
@@ -810,15 +819,31 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
   int max_ctx_now = 0;
   for (int b = 0; b < B; ++b) max_ctx_now = std::max(max_ctx_now, s->f[b] + K);
 
-  // passes of few rows keep their activations as operand tiles (the persistent
-  // pass stages rows)
   const int mt = M <= 16 ? 1 : 2;
   const bool persistent = pass_is_persistent(s, M);
-  const int tiled = dm.bf16 && M <= ROWS_MAX && !persistent;
+  // each activation array is laid out as the projection that reads it takes it:
+  // operand tiles for the few-row kernel, rows for the tiled kernels and the
+  // persistent pass
+  GemmPlan pq{}, po{}, p13{}, p2{}, pl{};
+  int tq = 0, to = 0, t13 = 0, t2 = 0, tl = 0;
+  if (dm.bf16) {
+    pq = pass_plan(s, M, Nqkv, d);
+    po = pass_plan(s, M, d, dm.Hq * D);
+    p13 = pass_plan(s, M, 2 * dm.dff, d);
+    p2 = pass_plan(s, M, d, dm.dff);
+    pl = pass_plan(s, lm_mode == 0 ? M : B, dm.Vimg, d);
+    if (!persistent) {
+      tq = pass_tiled(s, pq, M);
+      to = pass_tiled(s, po, M);
+      t13 = pass_tiled(s, p13, M);
+      t2 = pass_tiled(s, p2, M);
+      tl = pass_tiled(s, pl, M);
+    }
+  }
   const TokIn tok = io.tok ? TokIn{io.tok, K, io.tok_stride, io.tok_rows} : TokIn{s->tok, K, K, B};
   float* const logits = io.logits ? io.logits : s->logits;
   float* const x_last = io.h_pre ? io.h_pre : s->x;  // the last layer's residual
-  embed(dm, m->emb, tok, io.zero, io.n_zero, M, m->layers[0].g1, s->x, s->xn, s->xn_plane, tiled, s->ssq, st);
+  embed(dm, m->emb, tok, io.zero, io.n_zero, M, m->layers[0].g1, s->x, s->xn, s->xn_plane, tq, s->ssq, st);
   int ssq_parts = 1;
 
   EpiArgs base{};
@@ -843,16 +868,11 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
   base.q_plane = s->q_plane;
   base.xn_plane = s->xn_plane;
   base.h_plane = s->h_plane;
-  base.tiled = tiled;
 
   if (dm.bf16) {
     // algorithmic bytes: bf16 weights and KV, 4-byte activations (two bf16 planes), fp32 residual
     const double A = 4.0;
     const int X = m->xcd;
-    GemmPlan pq = gemm_plan_bf16(M, Nqkv, d, X);
-    GemmPlan po = gemm_plan_bf16(M, d, dm.Hq * D, X);
-    GemmPlan p13 = gemm_plan_bf16(M, 2 * dm.dff, d, X);
-    GemmPlan p2 = gemm_plan_bf16(M, d, dm.dff, X);
     AttnPlan pa = attn_plan(dm, B, K, max_ctx_now, X);
     // workspaces were sized at session creation for every plan the session can
     // meet; a plan outside them is a bug, refused before any launch
@@ -910,11 +930,12 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       HIPCHK(hipGetLastError());
       return false;
     }
-    auto rows_of = [&](const void* p, size_t plane, int ld) {
+    auto rows_of = [&](const void* p, size_t plane, int ld, int tiled) {
       return ActIn{(const uint16_t*)p, plane, ld, 0, 1, tiled};
     };
-    const ActIn in_x = rows_of(s->xn, s->xn_plane, d), in_o = rows_of(s->o, s->o_plane, dm.Hq * D),
-                in_h = rows_of(s->h, s->h_plane, dm.dff);
+    const ActIn in_q = rows_of(s->xn, s->xn_plane, d, tq), in_o = rows_of(s->o, s->o_plane, dm.Hq * D, to),
+                in_13 = rows_of(s->xn, s->xn_plane, d, t13), in_h = rows_of(s->h, s->h_plane, dm.dff, t2),
+                in_l = rows_of(s->xn, s->xn_plane, d, tl);
     // Where only each sequence's last row is asked for, nothing reads what the
     // other rows become behind the last layer's attention (their keys and
     // values are cached by then): that layer's O, gate/up and down projections
@@ -923,8 +944,9 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
     // gather's launch where it saves 16-row tiles, the step of the GEMMs' cost.
     // ssd_prefill to free of eight 256-token prompts, 8B widths, two layers:
     // 3155 -> 1999 us; of one 64-token prompt, 24 layers of the 1B widths: 1784 -> 1775.
+    // (operand tiles of the attention output are read by the few-row kernel alone.)
     const bool compact = lm_mode == 1 && io.last_state && (M + 15) / 16 > (B + 15) / 16 &&
-                         (size_t)B * d * 4 <= s->h_plane * 4;
+                         (size_t)B * d * 4 <= s->h_plane * 4 && (!to || pass_plan(s, B, d, dm.Hq * D).tile == 0);
     for (int l = 0; l < dm.L; ++l) {
       const LayerW& W = m->layers[l];
       char* kc = (char*)s->kc + (size_t)l * s->kv_layer_elems * es;
@@ -937,20 +959,21 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       e.kc = kc;
       e.vc = vc;
       m->prof.run(0, qkv_bytes, st, [&] {
-        gemm_bf16(pq, W.wqkv, Nqkv, d, in_x, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(pq, W.wqkv, Nqkv, d, in_q, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * Nqkv * d, pq.tile);
       m->prof.run(5, attn_bytes, st, [&] {
-        attention_bf16(dm, pa, B, K, s->d_f, s->q, s->q_plane, kc, vc, s->Lmax, s->o, s->o_plane, tiled, s->apart,
+        attention_bf16(dm, pa, B, K, s->d_f, s->q, s->q_plane, kc, vc, s->Lmax, s->o, s->o_plane, to, s->apart,
                        s->acnt, st);
       }, attn_flops);
       if (compact && l + 1 == dm.L) {
-        ssq_parts = last_layer_tail(s, K, base, in_o, st);
+        ssq_parts = last_layer_tail(s, K, base, in_o, pass_tiled(s, pl, B), st);
         continue;
       }
       e = base;
       e.kind = EPI_RESID;
       e.ssq = nullptr;
       e.gnext = W.g2;
+      e.tiled = t13;
       e.ld = d;
       m->prof.run(1, o_bytes, st, [&] {
         gemm_bf16(po, W.wo, d, dm.Hq * D, in_o, M, e, s->gpart, s->gcnt, st);
@@ -961,15 +984,17 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       e.ssq = s->ssq;
       e.ssq_parts = ssq_parts;
       e.h = s->h;
+      e.tiled = t2;
       e.ld = dm.dff;
       m->prof.run(2, gu_bytes, st, [&] {
-        gemm_bf16(p13, W.w13, 2 * dm.dff, d, in_x, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(p13, W.w13, 2 * dm.dff, d, in_13, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * 2 * dm.dff * d, p13.tile);
       e = base;
       e.kind = EPI_RESID;
       e.ssq = nullptr;
       e.gnext = (l + 1 < dm.L) ? m->layers[l + 1].g1 : m->gf;
       if (l + 1 == dm.L) e.xo = x_last;
+      e.tiled = l + 1 < dm.L ? tq : tl;
       e.ld = d;
       m->prof.run(3, dn_bytes, st, [&] {
         gemm_bf16(p2, W.w2, d, dm.dff, in_h, M, e, s->gpart, s->gcnt, st);
@@ -983,24 +1008,22 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
     e.logits = logits;
     e.ld = dm.Vimg;
     if (lm_mode == 0) {
-      GemmPlan pl = gemm_plan_bf16(M, dm.Vimg, d, X);
       if (gemm_partials_floats(pl, M) > s->gpart_cap || (size_t)gemm_counters(pl) > s->gcnt_cap)
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
       m->prof.run(4, (double)dm.Vimg * d * es + (double)M * d * A + (double)M * dm.Vimg * 4, st, [&] {
-        gemm_bf16(pl, m->wlm, dm.Vimg, d, in_x, M, e, s->gpart, s->gcnt, st);
+        gemm_bf16(pl, m->wlm, dm.Vimg, d, in_l, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * dm.Vimg * d, pl.tile);
     } else {
       if (!compact) {
         e.ssq_off = K - 1;
         e.ssq_step = K;
       }
-      GemmPlan pl = gemm_plan_bf16(B, dm.Vimg, d, X);
       if (gemm_partials_floats(pl, B) > s->gpart_cap || (size_t)gemm_counters(pl) > s->gcnt_cap)
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
       m->prof.run(4, (double)dm.Vimg * d * es + (double)B * d * A + (double)B * dm.Vimg * 4, st, [&] {
-        ActIn last = in_x;  // the last row of each sequence
+        ActIn last = in_l;  // the last row of each sequence
         if (compact) {
-          last.tiled = B <= ROWS_MAX;
+          last.tiled = pass_tiled(s, pl, B);
         } else {
           last.row0 = K - 1;
           last.rstep = K;
@@ -1112,9 +1135,12 @@ void size_workspaces(const Dims& dm, const ssd_model* m, int B, int P, int Kmax,
   for (int Mc : gemm_row_classes()) {
     for (auto nk : {std::make_pair(Nqkv, dm.d), std::make_pair(dm.d, dm.Hq * dm.D), std::make_pair(2 * dm.dff, dm.d),
                     std::make_pair(dm.d, dm.dff), std::make_pair(dm.Vimg, dm.d)}) {
-      GemmPlan p = gemm_plan_bf16(Mc, nk.first, nk.second, 0);  // sizes do not depend on the XCD mapping
-      gpart = std::max(gpart, gemm_partials_floats(p, Mc));
-      gcnt = std::max(gcnt, (size_t)gemm_counters(p));
+      for (auto plan : {gemm_plan_bf16, gemm_plan_guided}) {
+        if (plan == gemm_plan_guided && (Mc <= 64 || Mc > ROWS_MAX)) continue;  // the same there
+        const GemmPlan p = plan(Mc, nk.first, nk.second, 0);  // sizes do not depend on the XCD mapping
+        gpart = std::max(gpart, gemm_partials_floats(p, Mc));
+        gcnt = std::max(gcnt, (size_t)gemm_counters(p));
+      }
       if (nk.first == dm.d) ssq_parts_max = std::max(ssq_parts_max, gemm_max_parts(dm.d));
     }
   }
@@ -1586,11 +1612,9 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     e.ld = dm.Vimg;
     gemm_f32((const float*)m->wlm, dm.Vimg, d, (const float*)w.xn, d, R, e, st);
   } else {
-    base.tiled = R <= ROWS_MAX && (R + 15) / 16 * 16 <= w.plane_rows;
-    auto rows_of = [&](const void* p, size_t plane, int ld) {
-      return ActIn{(const uint16_t*)p, plane, ld, 0, 1, base.tiled};
+    auto rows_of = [&](const void* p, size_t plane, int ld, int tiled) {
+      return ActIn{(const uint16_t*)p, plane, ld, 0, 1, tiled};
     };
-    draft_input(hin, m->emb, tok, R, d, w.z, w.z_plane, base.tiled, st);
     const int X = m->xcd;
     auto plan = [&](int N, int K) {
       GemmPlan p = gemm_plan_bf16(R, N, K, X);
@@ -1599,37 +1623,41 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the draft head's workspace"};
       return p;
     };
+    const GemmPlan p0 = plan(d, 2 * d), p1 = plan(2 * mi, d), p2 = plan(d, mi), p3 = plan(dm.Vimg, d);
+    // each array as its reader takes it (tiles hold whole groups of 16 rows)
+    auto tiled = [&](const GemmPlan& p) { return plan_tiled(p, R) && (R + 15) / 16 * 16 <= w.plane_rows; };
+    const int t0 = tiled(p0), t1 = tiled(p1), t2 = tiled(p2), t3 = tiled(p3);
+    draft_input(hin, m->emb, tok, R, d, w.z, w.z_plane, t0, st);
     // u = W0 [h; e]; n = g * u (and the parts of sum u^2)
-    GemmPlan p0 = plan(d, 2 * d);
     EpiArgs e = base;
     e.kind = EPI_RESID;
     e.x = nullptr;
     e.gnext = h->g;
+    e.tiled = t1;
     e.ld = d;
-    gemm_bf16(p0, h->w0, d, 2 * d, rows_of(w.z, w.z_plane, 2 * d), R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p0, h->w0, d, 2 * d, rows_of(w.z, w.z_plane, 2 * d, t0), R, e, w.gpart, w.gcnt, st);
     // SwiGLU(n / rms(u))
-    GemmPlan p1 = plan(2 * mi, d);
     e = base;
     e.kind = EPI_SWIGLU;
     e.ssq = w.ssq;
     e.ssq_parts = gemm_parts(p0, d);
+    e.tiled = t2;
     e.ld = mi;
-    gemm_bf16(p1, h->w13, 2 * mi, d, rows_of(w.xn, w.xn_plane, d), R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p1, h->w13, 2 * mi, d, rows_of(w.xn, w.xn_plane, d, t1), R, e, w.gpart, w.gcnt, st);
     // h_hat = u + W2 (...); n = g_f * h_hat for the output layer
-    GemmPlan p2 = plan(d, mi);
     e = base;
     e.kind = EPI_RESID;
     e.gnext = m->gf;
+    e.tiled = t3;
     e.ld = d;
-    gemm_bf16(p2, h->w2, d, mi, rows_of(w.hb, w.hb_plane, mi), R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p2, h->w2, d, mi, rows_of(w.hb, w.hb_plane, mi, t2), R, e, w.gpart, w.gcnt, st);
     // GenHead(RMSNorm(h_hat)) over the image codes
-    GemmPlan p3 = plan(dm.Vimg, d);
     e = base;
     e.kind = EPI_LOGITS;
     e.ssq = w.ssq;
     e.ssq_parts = gemm_parts(p2, d);
     e.ld = dm.Vimg;
-    gemm_bf16(p3, m->wlm, dm.Vimg, d, rows_of(w.xn, w.xn_plane, d), R, e, w.gpart, w.gcnt, st);
+    gemm_bf16(p3, m->wlm, dm.Vimg, d, rows_of(w.xn, w.xn_plane, d, t3), R, e, w.gpart, w.gcnt, st);
   }
   first_token(R, dm.Vimg, dm.img_lo, logits, SSD_GREEDY, 0, 1.0, 0, nullptr, out, 1, st);
   HIPCHK(hipGetLastError());

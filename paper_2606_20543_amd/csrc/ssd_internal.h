@@ -3,8 +3,9 @@
 // Data layout in HBM (all row-major unless stated):
 //   residual x        fp32 [M][d]
 //   xn                act [M][d]              g * x: the GEMM input after an RMSNorm
-//                     (act arrays: 16x32 tiles in passes of at most ROWS_MAX
-//                     rows, row-major in larger ones; see act_index)
+//                     (act arrays: 16x32 tiles where the few-row kernel reads
+//                     them in passes of at most ROWS_MAX rows, else row-major;
+//                     see act_index)
 //   ssq               fp32 [parts][Mmax]      partial sums of x^2 per token (producer feature blocks)
 //   q                 act [B][Hkv][rows_pad x D as 16x32 tiles]   bf16 models; query row
 //                     r = head_in_group * K + k, rows_pad = K*g rounded up to 32
@@ -135,7 +136,7 @@ __host__ __device__ inline int q_rows_pad(int K, int g) { return ((K * g + 31) /
 // accepts (one per 64-feature block: d_model <= 8192).
 constexpr int GEMM_RMS_MAX_PARTS = 128;
 // Most rows of a pass whose projections run on the few-row kernel
-constexpr int ROWS_MAX = 64;
+constexpr int ROWS_MAX = 128;
 
 // GEMM launch plan for one (M, N, K) problem.  tile 0: the few-row kernel, 16 NT
 // features and 16 MT rows per workgroup, K split S ways (n_fb counts 64-feature
@@ -166,11 +167,11 @@ inline int gemm_counters(const GemmPlan& p) {
   return p.tile ? p.n_fb * p.m_tiles : gemm_parts(p, p.n_fb * p.bn);
 }
 // Row counts that cover every plan class: the few-row kernel's (up to 16, 32,
-// 48 and 64 rows), 65..128 and each count of 128-row tiles up to 256 (a
+// 48, 64, 96 and 128 rows) and each count of 128-row tiles up to 256 (a
 // split plan has fewer than 256 output tiles).  Sizing a workspace over these bounds every
 // plan of any row count.
 inline std::vector<int> gemm_row_classes() {
-  std::vector<int> v = {1, 16, 17, 32, 33, 64, 65, 128};
+  std::vector<int> v = {1, 16, 17, 32, 33, 48, 49, 64, 65, 96, 97, 128};
   for (int t = 2; t <= 256; ++t) v.push_back(128 * t);
   return v;
 }
@@ -231,8 +232,18 @@ inline void launch_timed(Kern kernel, dim3 grid, dim3 block, hipStream_t st, Arg
 
 // ---- launchers (kernels_*.hip) ----
 GemmPlan gemm_plan_bf16(int M, int N, int K, int xcd);
+// the same for passes of guided sessions: the tiled kernels from 65 rows on.  The
+// guidance weight multiplies the rounding of the two streams' scores, and a code
+// sampled from thousands that share a long tail follows it: with the few-row
+// kernel's order of sums 0.7 % of the codes drawn at weight 5 and top-k 2000 came
+// out as a neighbour (none of the accept decisions, and no closer to or further
+// from 64-bit scores).  Guided decodes keep the codes they gave.
+GemmPlan gemm_plan_guided(int M, int N, int K, int xcd);
 size_t gemm_partials_floats(const GemmPlan& p, int M);
-GemmPlan gemm_rows_plan(int M, int N, int K, int xcd);  // (part of gemm_plan_bf16)
+// (part of gemm_plan_bf16) ns: the modelled time
+GemmPlan gemm_rows_plan(int M, int N, int K, int xcd, double* ns = nullptr);
+// the plan reads its input as operand tiles (act_index)
+inline int plan_tiled(const GemmPlan& p, int M) { return p.tile == 0 && M <= ROWS_MAX; }
 // y = W x for M split input rows; epilogue per `epi`.
 void gemm_bf16(const GemmPlan& p, const void* Wpacked, int N, int K, const ActIn& in, int M, const EpiArgs& epi,
                float* partials, unsigned* counters, hipStream_t st);
