@@ -53,7 +53,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16
 GEMM_SRCS = [os.path.join(ROOT, "paper_2606_20543_amd", "csrc", f)
              for f in ("kernels_gemm.hip", "gemm_rows.h", "tiles.h", "ssd_internal.h")]
 TRAFFIC_FILES = {
-    "stream": os.path.join(ROOT, "profiles", "gemm_bf16_1b-24x24_traffic.md"),
+    "stream": os.path.join(ROOT, "profiles", "gemm_rows_1b-24x24_traffic.md"),
     "tiled": os.path.join(ROOT, "profiles", "gemm_tile_8b-64x64-b8_traffic.md"),
 }
 GEMM_CLASSES = ("qkv", "o_proj", "gate_up", "down", "lm_head")
