@@ -43,10 +43,14 @@ struct HipError {
   const char* what;
 };
 
-#define HIPCHK(x)                                 \
-  do {                                            \
-    hipError_t e_ = (x);                          \
-    if (e_ != hipSuccess) throw HipError{e_, #x}; \
+// (the runtime keeps a failed call's error for its thread: taken here, or the next call of the library would find it)
+#define HIPCHK(x)                \
+  do {                           \
+    hipError_t e_ = (x);         \
+    if (e_ != hipSuccess) {      \
+      (void)hipGetLastError();   \
+      throw HipError{e_, #x};    \
+    }                            \
   } while (0)
 
 // host or device pointer?
@@ -180,22 +184,29 @@ struct Allocs {
   }
 };
 
-// A set of arrays in one device block: laid out once to measure it (get
-// returns nullptr), then again to hand the addresses out.
-// The current device's own memory (not managed, not another GPU's): kernels may
-// read and write a caller's array there in place of a copy.  Vector accesses
-// need it aligned.
-bool is_local_ptr(const void* p, size_t align) {
+// `bytes` of the current device's own memory (not managed, not another GPU's), all
+// inside the allocation p points into: kernels may read and write a caller's
+// array there in place of a copy.  Vector accesses need it aligned.  An array
+// that ends early goes through a copy, which the runtime checks against the
+// allocation and refuses.
+bool is_local_ptr(const void* p, size_t align, size_t bytes) {
   if (!p || ((uintptr_t)p & (align - 1))) return false;
   hipPointerAttribute_t attr;
   int dev = -1;
-  if (hipPointerGetAttributes(&attr, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&attr, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+      attr.type != hipMemoryTypeDevice || attr.device != dev ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return attr.type == hipMemoryTypeDevice && attr.device == dev;
+  const size_t at = (size_t)((const char*)p - (const char*)base);
+  return at <= size && bytes <= size - at;
 }
 
+// A set of arrays in one device block: laid out once to measure it (get
+// returns nullptr), then again to hand the addresses out.
 struct Arena {
   char* base = nullptr;
   size_t off = 0;
@@ -1818,8 +1829,9 @@ ssd_status ssd_draft_head_run(ssd_draft_head* h, int32_t R, const float* hs, con
   try {
     const HeadWork& w = h->work;
     // arrays in this GPU's memory are read and written in place, the others staged
-    const bool h_local = is_local_ptr(hs, 16), t_local = is_local_ptr(tokens, 4), d_local = is_local_ptr(drafts, 4),
-               l_local = is_local_ptr(logits_out, 16);
+    const size_t hb = (size_t)R * d * 4, tb = (size_t)R * 4, lb = (size_t)R * dm.Vimg * 4;
+    const bool h_local = is_local_ptr(hs, 16, hb), t_local = is_local_ptr(tokens, 4, tb),
+               d_local = is_local_ptr(drafts, 4, tb), l_local = is_local_ptr(logits_out, 16, lb);
     if (!h_local) HIPCHK(hipMemcpyAsync(w.hin, hs, (size_t)R * d * 4, hipMemcpyDefault, st));
     if (!t_local) HIPCHK(hipMemcpyAsync(w.tok, tokens, (size_t)R * 4, hipMemcpyDefault, st));
     head_forward(h, w, R, h_local ? hs : w.hin, t_local ? tokens : w.tok, d_local ? drafts : w.out,
@@ -1907,8 +1919,9 @@ ssd_status ssd_draft_head_run_noalloc(ssd_draft_head* h, int32_t R, const float*
     // the array keeps the last call's contents: counters and the block-start lookup start at zero
     fill_u32(w.gcnt, gcnt, 0u, st);
     fill_u32((unsigned*)w.f0, 1, 0u, st);
-    const bool h_local = is_local_ptr(hs, 16), t_local = is_local_ptr(tokens, 4), d_local = is_local_ptr(drafts, 4),
-               l_local = is_local_ptr(logits_out, 16);
+    const size_t hb = (size_t)R * d * 4, tb = (size_t)R * 4, lb = (size_t)R * dm.Vimg * 4;
+    const bool h_local = is_local_ptr(hs, 16, hb), t_local = is_local_ptr(tokens, 4, tb),
+               d_local = is_local_ptr(drafts, 4, tb), l_local = is_local_ptr(logits_out, 16, lb);
     if (!h_local) HIPCHK(hipMemcpyAsync(w.hin, hs, r * d * 4, hipMemcpyDeviceToDevice, st));
     if (!t_local) HIPCHK(hipMemcpyAsync(w.tok, tokens, r * 4, hipMemcpyDeviceToDevice, st));
     head_forward(h, w, R, h_local ? hs : w.hin, t_local ? tokens : w.tok, d_local ? drafts : w.out,
@@ -2036,10 +2049,13 @@ ssd_status ssd_verify_step(ssd_session* s, int32_t K, int32_t* tokens, const flo
   hipStream_t st = s->stream;
   // arrays in this GPU's memory are read and written in place; the others are
   // staged through the session's
-  const bool tok_local = is_local_ptr(tokens, 4), acc_local = is_local_ptr(accept_mask, 1),
-             cnt_local = is_local_ptr(accept_count, 4), log_local = is_local_ptr(logits_out, 16),
-             h_local = is_local_ptr(h_pre_out, 16) && !s->cfg && !pass_is_persistent(s, B * K),
-             ref_local = is_local_ptr(ref_logits, 4);
+  const size_t rows = (size_t)nb * K, row_b = (size_t)dm.Vimg * 4;
+  const bool direct = !s->cfg && !pass_is_persistent(s, B * K);  // the pass writes the caller's rows itself
+  const bool tok_local = is_local_ptr(tokens, 4, rows * 4), acc_local = is_local_ptr(accept_mask, 1, rows),
+             cnt_local = is_local_ptr(accept_count, 4, (size_t)nb * 4),
+             log_local = is_local_ptr(logits_out, 16, rows * row_b),
+             h_local = direct && is_local_ptr(h_pre_out, 16, rows * dm.d * 4),
+             ref_local = is_local_ptr(ref_logits, 4, rows * row_b);
   try {
     int* const tok = tok_local ? tokens : s->tok;
     int* const cnt = cnt_local && !prm->commit ? accept_count : s->cnt;
@@ -2060,7 +2076,7 @@ ssd_status ssd_verify_step(ssd_session* s, int32_t K, int32_t* tokens, const flo
     io.zero = prm->commit ? nullptr : cnt;
     io.n_zero = prm->commit ? 0 : nb;
     io.h_pre = h_local ? h_pre_out : nullptr;
-    if (log_local && !s->cfg && !pass_is_persistent(s, B * K)) io.logits = logits_out;
+    if (log_local && direct) io.logits = logits_out;
     io.last_state = !h_pre_out;
     run_forward(s, K, all_rows ? 0 : 1, io);
     // per-image scores: the pass's own logits, or the guided mix of the two streams
