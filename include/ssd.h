@@ -114,7 +114,8 @@ void ssd_free_model(ssd_model* model);
 ssd_status ssd_prefill(ssd_model* model, int32_t B, int32_t P, const int32_t* prefix, int32_t max_ctx,
                        int32_t max_block, void* stream, ssd_session** out);
 
-/* Waits for the session's work.  Its workspace (if at most 1/32 of the GPU's
+/* Waits for the session's work.  May be called after the model has been freed
+ * (no other call on the session may).  The workspace (if at most 1/32 of the GPU's
  * memory, and one per model) stays with the model for its next session; it is
  * freed with the model, or when an allocation of the library needs the memory. */
 void ssd_free_session(ssd_session* sess);

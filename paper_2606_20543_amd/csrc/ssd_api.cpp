@@ -1471,7 +1471,8 @@ ssd_status ssd_init_model(const ssd_model_config* cfg, const void* weights, void
 
 void ssd_free_session(ssd_session* s) {
   if (!s) return;
-  if (s->m && s->m->dec == s) s->m->dec = nullptr;
+  // (nothing of the model is read here: it may be gone; its decode workspace is
+  // a session that no caller holds)
   // the workspace stays with the model once the session's work has finished
   if (hipStreamSynchronize(s->stream) == hipSuccess && !s->poisoned && s->pool) {
     s->pool->give(s->block, s->block_bytes);

@@ -157,6 +157,18 @@ int main() {
     CHECK(gp2 >= gp && gc2 >= gc && ap2 >= ap && ac2 >= ac && parts2 >= parts);
     CHECK(parts >= 1);
   }
+  // 6. a session may be freed after its model (nothing on a device here: the calls into the runtime fail)
+  {
+    auto* m = new ssd_model();
+    m->dm = dims_of(shapes[1]);
+    auto* s = new ssd_session();
+    s->m = m;
+    s->dm = m->dm;
+    s->stream = nullptr;
+    s->pool = m->pool;
+    ssd_free_model(m);
+    ssd_free_session(s);
+  }
   if (g_fail) {
     std::fprintf(stderr, "%d checks failed\n", g_fail);
     return 1;
