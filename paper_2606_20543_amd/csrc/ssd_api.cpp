@@ -1675,6 +1675,54 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
   HIPCHK(hipGetLastError());
 }
 
+// Workspace of an allocation-free run of R rows: byte offsets in the static array
+// (every region 256-byte aligned), their end, and the sizes a HeadWork names.
+// The x^2 partial sums take the place of the staged states: at most one part per
+// two columns, first written when the first kernel has read those.
+struct NoallocLayout {
+  size_t cnt, f0, tok, out, hin, z, x, xn, hb, logits, part, need;
+  size_t gpart = 0, gcnt = 0, plane_rows;
+  int parts;
+};
+NoallocLayout noalloc_layout(const Dims& dm, int mi, int R, int xcd) {
+  NoallocLayout l;
+  const int d = dm.d;
+  l.parts = dm.bf16 ? 1 : f32_feature_blocks(d);
+  if (dm.bf16) {
+    const std::pair<int, int> nk[4] = {{d, 2 * d}, {2 * mi, d}, {d, mi}, {dm.Vimg, d}};
+    for (const auto& p : nk) {
+      GemmPlan pl = gemm_plan_bf16(R, p.first, p.second, xcd);
+      l.gpart = std::max(l.gpart, gemm_partials_floats(pl, R));
+      l.gcnt = std::max(l.gcnt, (size_t)gemm_counters(pl));
+      if (p.first == d) l.parts = std::max(l.parts, gemm_parts(pl, d));
+    }
+  }
+  const size_t r = (size_t)R;
+  auto carve = [&](size_t plane_rows) {
+    l.need = 0;
+    l.plane_rows = plane_rows;
+    auto take = [&](size_t bytes) {
+      const size_t at = l.need;
+      l.need += (bytes + 255) & ~(size_t)255;
+      return at;
+    };
+    l.cnt = take(l.gcnt * 4);
+    l.f0 = take(4);
+    l.tok = take(r * 4);
+    l.out = take(r * 4);
+    l.hin = take(r * d * 4);
+    l.z = take(plane_rows * 2 * d * 4);
+    l.x = take(r * d * 4);
+    l.xn = take(plane_rows * d * 4);
+    l.hb = take(plane_rows * mi * 4);
+    l.logits = take(r * dm.Vimg * 4);
+    l.part = take(l.gpart * 4);
+  };
+  carve(dm.bf16 && R <= ROWS_MAX ? (r + 15) / 16 * 16 : r);  // tiled layouts hold whole groups of 16 rows
+  if (l.need > NOALLOC_SCRATCH_BYTES && l.plane_rows > r) carve(r);  // without the padding (row-major planes) it may still fit
+  return l;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1861,64 +1909,37 @@ ssd_status ssd_draft_head_run_noalloc(ssd_draft_head* h, int32_t R, const float*
   if (!m->scratch) return fail(SSD_E_STATE, "the static workspace's device address is unknown");
   const Dims& dm = m->dm;
   const int d = h->d, mi = h->mi;
-  // carve this call's workspace out of the static array: every region 256-byte aligned
-  size_t gpart = 0, gcnt = 0;
-  int parts = dm.bf16 ? 1 : f32_feature_blocks(d);
-  if (dm.bf16) {
-    const std::pair<int, int> nk[4] = {{d, 2 * d}, {2 * mi, d}, {d, mi}, {dm.Vimg, d}};
-    for (const auto& p : nk) {
-      GemmPlan pl = gemm_plan_bf16(R, p.first, p.second, m->xcd);
-      gpart = std::max(gpart, gemm_partials_floats(pl, R));
-      gcnt = std::max(gcnt, (size_t)gemm_counters(pl));
-      if (p.first == d) parts = std::max(parts, gemm_parts(pl, d));
-    }
-  }
-  const size_t r = (size_t)R;
-  size_t rp = dm.bf16 && R <= ROWS_MAX ? (r + 15) / 16 * 16 : r;  // rows of the planes (tiled layouts)
-  size_t off[12], need = 0;
-  auto carve = [&]() {
-    const size_t sz[12] = {gcnt * 4, 4, r * 4, r * 4, r * d * 4, rp * 2 * d * 4, r * d * 4, rp * d * 4,
-                           (size_t)parts * r * 4, rp * mi * 4, r * dm.Vimg * 4, gpart * 4};
-    need = 0;
-    for (int i = 0; i < 12; ++i) {
-      off[i] = need;
-      need += (sz[i] + 255) & ~(size_t)255;
-    }
-  };
-  carve();
-  if (need > NOALLOC_SCRATCH_BYTES && rp > r) {  // without the padding (row-major planes) it may still fit
-    rp = r;
-    carve();
-  }
-  if (need > NOALLOC_SCRATCH_BYTES)
-    return fail(SSD_E_INVAL, "R = %d rows need %zu bytes of workspace; the static workspace holds %zu", R, need,
+  const NoallocLayout lay = noalloc_layout(dm, mi, R, m->xcd);
+  if (lay.need > NOALLOC_SCRATCH_BYTES)
+    return fail(SSD_E_INVAL, "R = %d rows need %zu bytes of workspace; the static workspace holds %zu", R, lay.need,
                 NOALLOC_SCRATCH_BYTES);
+  const size_t r = (size_t)R, rp = lay.plane_rows;
   char* base = (char*)m->scratch;
   HeadWork w;
   w.rows = R;
-  w.gcnt = (unsigned*)(base + off[0]);
-  w.gcnt_cap = gcnt;
-  w.f0 = (int*)(base + off[1]);
-  w.tok = (int*)(base + off[2]);
-  w.out = (int*)(base + off[3]);
-  w.hin = (float*)(base + off[4]);
-  w.z = base + off[5];
+  w.gcnt = (unsigned*)(base + lay.cnt);
+  w.gcnt_cap = lay.gcnt;
+  w.f0 = (int*)(base + lay.f0);
+  w.tok = (int*)(base + lay.tok);
+  w.out = (int*)(base + lay.out);
+  w.hin = (float*)(base + lay.hin);
+  w.z = base + lay.z;
   w.plane_rows = (int)rp;
   w.z_plane = rp * 2 * d;
-  w.x = (float*)(base + off[6]);
-  w.xn = base + off[7];
+  w.x = (float*)(base + lay.x);
+  w.xn = base + lay.xn;
   w.xn_plane = rp * d;
-  w.ssq = (float*)(base + off[8]);
-  w.ssq_cap = parts;
-  w.hb = base + off[9];
+  w.ssq = w.hin;
+  w.ssq_cap = lay.parts;
+  w.hb = base + lay.hb;
   w.hb_plane = rp * mi;
-  w.logits = (float*)(base + off[10]);
-  w.gpart = (float*)(base + off[11]);
-  w.gpart_cap = gpart;
+  w.logits = (float*)(base + lay.logits);
+  w.gpart = (float*)(base + lay.part);
+  w.gpart_cap = lay.gpart;
   hipStream_t st = m->stream;
   try {
     // the array keeps the last call's contents: counters and the block-start lookup start at zero
-    fill_u32(w.gcnt, gcnt, 0u, st);
+    fill_u32(w.gcnt, lay.gcnt, 0u, st);
     fill_u32((unsigned*)w.f0, 1, 0u, st);
     const size_t hb = (size_t)R * d * 4, tb = (size_t)R * 4, lb = (size_t)R * dm.Vimg * 4;
     const bool h_local = is_local_ptr(hs, 16, hb), t_local = is_local_ptr(tokens, 4, tb),

@@ -169,6 +169,38 @@ int main() {
     ssd_free_model(m);
     ssd_free_session(s);
   }
+  // 7. the allocation-free head run takes every size whose staged inputs, activations, logits and one set of
+  // x^2 sums fit the static array, as long as the split-K partials of its GEMMs fit beside them: sizes at that
+  // limit (bf16: R, d, m, V_img), and fp32 heads, which have no partials
+  const int at_limit[][4] = {{111, 2560, 256, 126016}, {108, 4864, 256, 107456},  {123, 7168, 768, 84704},
+                             {98, 6656, 1280, 119104}, {108, 6912, 1792, 101792}, {92, 6144, 768, 125088},
+                             {65, 4096, 8192, 65536},  {96, 2048, 4096, 16384},   {128, 2048, 4096, 16384}};
+  for (const auto& c : at_limit) {
+    Dims dm = dims_of(shapes[1]);
+    dm.d = c[1];
+    dm.Vimg = c[3];
+    const NoallocLayout l = noalloc_layout(dm, c[2], c[0], 8);
+    CHECK(l.need <= NOALLOC_SCRATCH_BYTES);
+    CHECK((size_t)l.parts * c[0] * 4 <= l.z - l.hin);
+  }
+  for (int d : {2, 30, 64, 250, 256, 1024, 4096}) {
+    for (int V : {2, 70, 1024, 50000}) {
+      Dims dm = dims_of(shapes[0]);
+      dm.d = d;
+      dm.Vimg = V;
+      auto plain = [&](size_t r) {  // counters, zero, ids and drafts, states, z, x, xn, one x^2 sum, h, logits
+        size_t n = 256;
+        for (size_t b : {r * 4, r * 4, r * d * 4, r * 2 * d * 4, r * d * 4, r * d * 4, r * 4, r * 512 * 4, r * V * 4})
+          n += (b + 255) & ~(size_t)255;
+        return n;
+      };
+      int R = 1;
+      while (plain(R + 1) <= NOALLOC_SCRATCH_BYTES && R < 65536) ++R;
+      const NoallocLayout l = noalloc_layout(dm, 512, R, 0);
+      CHECK(l.need <= NOALLOC_SCRATCH_BYTES);
+      CHECK((size_t)l.parts * R * 4 <= l.z - l.hin);
+    }
+  }
   if (g_fail) {
     std::fprintf(stderr, "%d checks failed\n", g_fail);
     return 1;
