@@ -749,6 +749,7 @@ struct PassIo {
   int* zero = nullptr;       // cleared by the pass's first kernel
   int n_zero = 0;
   bool last_state = false;   // no caller reads the final states of other rows than each sequence's last
+  bool prompt = false;       // a prefix pass (PassShape)
 };
 
 // a pass whose projections and attention run as one launch
@@ -756,31 +757,39 @@ bool pass_is_persistent(const ssd_session* s, int M) {
   return s->dm.bf16 && s->fw.on && M <= FWD_MAX_M && s->m->fwd_grid[M <= 16 ? 0 : 1] > 0;
 }
 
-GemmPlan pass_plan(const ssd_session* s, int M, int N, int K) {
-  return (s->cfg ? gemm_plan_guided : gemm_plan_bf16)(M, N, K, s->m->xcd);
-}
-// whether p's input is written as operand tiles (the 128 x 64 tiles, which run
-// guided passes from 65 rows on, write rows)
-int pass_tiled(const ssd_session* s, const GemmPlan& p, int M) { return plan_tiled(p, M) && !(s->cfg && M > 64); }
+// How the projections of a pass are planned.  A guided session's blocks take
+// gemm_plan_guided; prompts take the plans of any other pass, since
+// ssd_prefill does not know whether its session will be guided (a decode does,
+// and its prompts must leave the same keys and values).
+struct PassShape {
+  bool guided;
+  int xcd;
+  PassShape(const ssd_session* s, bool prompt) : guided(s->cfg && !prompt), xcd(s->m->xcd) {}
+  GemmPlan plan(int M, int N, int K) const { return (guided ? gemm_plan_guided : gemm_plan_bf16)(M, N, K, xcd); }
+  // whether p's input is written as operand tiles (the 128 x 64 tiles, which
+  // run guided blocks from 65 rows on, write rows)
+  int tiled(const GemmPlan& p, int M) const { return plan_tiled(p, M) && !(guided && M > 64); }
+};
 
 // The last layer behind its attention for the last row of each sequence only
 // (base: the pass's epilogue arguments; in_o: the attention output of all rows).
 // Leaves the rows' final states in s->x [B][d] and the output layer's inputs in
 // s->xn and s->ssq; returns the count of x^2 parts.
-int last_layer_tail(ssd_session* s, int K, const EpiArgs& base, ActIn in_o, int lm_tiled, hipStream_t st) {
+int last_layer_tail(ssd_session* s, const PassShape& ps, int K, const EpiArgs& base, ActIn in_o, int lm_tiled,
+                    hipStream_t st) {
   const Dims& dm = s->dm;
   ssd_model* m = s->m;
   const int B = s->B, d = dm.d, qd = dm.Hq * dm.D, dff = dm.dff;
   const double A = 4.0, es = (double)esize(dm);
   const LayerW& W = m->layers[dm.L - 1];
-  const GemmPlan po = pass_plan(s, B, d, qd), p13 = pass_plan(s, B, 2 * dff, d), p2 = pass_plan(s, B, d, dff);
+  const GemmPlan po = ps.plan(B, d, qd), p13 = ps.plan(B, 2 * dff, d), p2 = ps.plan(B, d, dff);
   for (const GemmPlan* gp : {&po, &p13, &p2})
     if (gemm_partials_floats(*gp, B) > s->gpart_cap || (size_t)gemm_counters(*gp) > s->gcnt_cap)
       throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
   if (gemm_parts(po, d) > s->ssq_parts_cap || gemm_parts(p2, d) > s->ssq_parts_cap)
     throw HipError{hipErrorInvalidValue, "rms partial sums exceed their buffer"};
-  const ActIn in_x{(const uint16_t*)s->xn, s->xn_plane, d, 0, 1, pass_tiled(s, p13, B)},
-      in_h{(const uint16_t*)s->h, s->h_plane, dff, 0, 1, pass_tiled(s, p2, B)};
+  const ActIn in_x{(const uint16_t*)s->xn, s->xn_plane, d, 0, 1, ps.tiled(p13, B)},
+      in_h{(const uint16_t*)s->h, s->h_plane, dff, 0, 1, ps.tiled(p2, B)};
   float* const xl = (float*)s->h;
   last_rows(s->x, B, K, d, xl, st);
   in_o.row0 = K - 1;
@@ -832,23 +841,24 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
 
   const int mt = M <= 16 ? 1 : 2;
   const bool persistent = pass_is_persistent(s, M);
+  const PassShape ps(s, io.prompt);
   // each activation array is laid out as the projection that reads it takes it:
   // operand tiles for the few-row kernel, rows for the tiled kernels and the
   // persistent pass
   GemmPlan pq{}, po{}, p13{}, p2{}, pl{};
   int tq = 0, to = 0, t13 = 0, t2 = 0, tl = 0;
   if (dm.bf16) {
-    pq = pass_plan(s, M, Nqkv, d);
-    po = pass_plan(s, M, d, dm.Hq * D);
-    p13 = pass_plan(s, M, 2 * dm.dff, d);
-    p2 = pass_plan(s, M, d, dm.dff);
-    pl = pass_plan(s, lm_mode == 0 ? M : B, dm.Vimg, d);
+    pq = ps.plan(M, Nqkv, d);
+    po = ps.plan(M, d, dm.Hq * D);
+    p13 = ps.plan(M, 2 * dm.dff, d);
+    p2 = ps.plan(M, d, dm.dff);
+    pl = ps.plan(lm_mode == 0 ? M : B, dm.Vimg, d);
     if (!persistent) {
-      tq = pass_tiled(s, pq, M);
-      to = pass_tiled(s, po, M);
-      t13 = pass_tiled(s, p13, M);
-      t2 = pass_tiled(s, p2, M);
-      tl = pass_tiled(s, pl, M);
+      tq = ps.tiled(pq, M);
+      to = ps.tiled(po, M);
+      t13 = ps.tiled(p13, M);
+      t2 = ps.tiled(p2, M);
+      tl = ps.tiled(pl, M);
     }
   }
   const TokIn tok = io.tok ? TokIn{io.tok, K, io.tok_stride, io.tok_rows} : TokIn{s->tok, K, K, B};
@@ -957,7 +967,7 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
     // 3155 -> 1999 us; of one 64-token prompt, 24 layers of the 1B widths: 1784 -> 1775.
     // (operand tiles of the attention output are read by the few-row kernel alone.)
     const bool compact = lm_mode == 1 && io.last_state && (M + 15) / 16 > (B + 15) / 16 &&
-                         (size_t)B * d * 4 <= s->h_plane * 4 && (!to || pass_plan(s, B, d, dm.Hq * D).tile == 0);
+                         (size_t)B * d * 4 <= s->h_plane * 4 && (!to || ps.plan(B, d, dm.Hq * D).tile == 0);
     for (int l = 0; l < dm.L; ++l) {
       const LayerW& W = m->layers[l];
       char* kc = (char*)s->kc + (size_t)l * s->kv_layer_elems * es;
@@ -977,7 +987,7 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
                        s->acnt, st);
       }, attn_flops);
       if (compact && l + 1 == dm.L) {
-        ssq_parts = last_layer_tail(s, K, base, in_o, pass_tiled(s, pl, B), st);
+        ssq_parts = last_layer_tail(s, ps, K, base, in_o, ps.tiled(pl, B), st);
         continue;
       }
       e = base;
@@ -1034,7 +1044,7 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       m->prof.run(4, (double)dm.Vimg * d * es + (double)B * d * A + (double)B * dm.Vimg * 4, st, [&] {
         ActIn last = in_l;  // the last row of each sequence
         if (compact) {
-          last.tiled = pass_tiled(s, pl, B);
+          last.tiled = ps.tiled(pl, B);
         } else {
           last.row0 = K - 1;
           last.rstep = K;
@@ -1315,6 +1325,7 @@ ssd_status create_session(ssd_model* m, int B, int P, int Lmax_req, int Kmax, hi
 bool prefill_pass(ssd_session* s) {
   PassIo io;
   io.last_state = true;
+  io.prompt = true;
   const bool compact = run_forward(s, s->P, 1, io);
   commit_update(s->B, -s->P, s->dm.Vimg, s->logits, s->carry, s->d_f, s->ref_flag, s->ring, s->stream);
   for (int b = 0; b < s->B; ++b) s->f[b] = s->P;

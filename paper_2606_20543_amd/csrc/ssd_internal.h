@@ -232,12 +232,13 @@ inline void launch_timed(Kern kernel, dim3 grid, dim3 block, hipStream_t st, Arg
 
 // ---- launchers (kernels_*.hip) ----
 GemmPlan gemm_plan_bf16(int M, int N, int K, int xcd);
-// the same for passes of guided sessions: the tiled kernels from 65 rows on.  The
+// the same for the blocks of guided sessions: the tiled kernels from 65 rows on.  The
 // guidance weight multiplies the rounding of the two streams' scores, and a code
 // sampled from thousands that share a long tail follows it: with the few-row
 // kernel's order of sums 0.7 % of the codes drawn at weight 5 and top-k 2000 came
 // out as a neighbour (none of the accept decisions, and no closer to or further
-// from 64-bit scores).  Guided decodes keep the codes they gave.
+// from 64-bit scores).  Guided blocks of these sizes keep the order of sums, and so
+// the codes, that they had; prompts take the common plans (PassShape).
 GemmPlan gemm_plan_guided(int M, int N, int K, int xcd);
 size_t gemm_partials_floats(const GemmPlan& p, int M);
 // (part of gemm_plan_bf16) ns: the modelled time

@@ -152,3 +152,36 @@ def wide():
 def test_guided_rounds_bf16(wide, rule, top_k):
     stats = _rounds(BF16, wide, 1, 40, ((24, 2), (5, 1)), rule, top_k)
     print("bf16 guided max logit error", stats["max_logit_err"], flush=True)
+
+
+def test_prompts_run_alike_stepwise_and_in_a_decode(wide):
+    """ssd_prefill does not know that its session will be guided; a guided decode does.  Both must run a prompt of
+    65 to 128 rows on the same kernels, so that they leave the same keys and values: the launches of the tiled
+    GEMMs are counted (the blocks after it are of at most 8 rows, which never take them)."""
+    Bi, P_, W_ = 1, 40, 4
+    pre = _prompts(BF16, Bi, P_)
+    drafts = (synth.random_codes(BF16, (Bi, 1, W_)) + BF16.img_lo).astype(np.int32)
+    out = np.zeros((Bi, 1, W_), np.int32)
+    sc = _sched(R.RULE_GREEDY)
+    sc.grid_h, sc.grid_w = 1, W_
+    tiled = []
+    for stepwise in (True, False):
+        ssd.ssd_profile_read(wide.model, reset=True)
+        ssd.ssd_profile(wide.model, True)
+        try:
+            if stepwise:
+                sess = ssd.ssd_prefill(wide.model, 2 * Bi, P_, pre, P_ + W_, W_)
+                ssd.ssd_session_set_cfg(sess, WEIGHT)
+                carry = np.zeros((Bi, BF16.v_img), np.float32)
+                ssd.ssd_get_carry(sess, carry)
+                blk = drafts[:, 0].copy()
+                blk[:, 0] = carry.argmax(1) + BF16.img_lo
+                want = G.gpu_verify(sess, BF16, blk, G.vparams(n_fixed=1))["tokens"]
+                ssd.ssd_free_session(sess)
+            else:
+                ssd.ssd_decode_image(wide.model, sc, Bi, P_, pre, drafts, out)
+        finally:
+            ssd.ssd_profile(wide.model, False)
+        tiled.append(ssd.ssd_profile_read(wide.model, reset=True)["tiled_gemm"][1])
+    assert tiled[0] == tiled[1]
+    assert np.array_equal(out[:, 0], want)
