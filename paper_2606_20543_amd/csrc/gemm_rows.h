@@ -370,8 +370,8 @@ GemmPlan gemm_rows_plan(int M, int N, int K, int xcd, double* ns) {
   p.S = S;
   p.KCB = KB / S;
   p.kchunks = 1;
-  p.bn = 64;
-  p.n_fb = (N + 63) / 64;
+  p.bn = NT * 16;
+  p.n_fb = (tiles + NT - 1) / NT;
   p.tail_S = 1;
   if (ns) *ns = best;
   return p;

@@ -1093,7 +1093,7 @@ size_t gemm_partials_floats(const GemmPlan& p, int M) {
   if (p.S <= 1) return 0;
   if (p.tile) return (size_t)p.S * p.m_tiles * TILE_ROWS * p.n_fb * p.bn;
   (void)M;
-  return (size_t)p.S * gemm_counters(p) * p.NT * p.MT * 256;
+  return (size_t)p.S * p.n_fb * p.NT * p.MT * 256;
 }
 
 void gemm_bf16(const GemmPlan& p, const void* Wpacked, int N, int K, const ActIn& in, int M, const EpiArgs& epi,
@@ -1160,7 +1160,7 @@ void gemm_bf16(const GemmPlan& p, const void* Wpacked, int N, int K, const ActIn
     a.W = Wpacked;
     a.N = N;
     a.KB = K / 32;
-    a.n_fb = gemm_parts(p, N);
+    a.n_fb = p.n_fb;
     a.S = p.S;
     a.xcd = p.S > 1 ? p.xcd : 0;
     a.in = in;

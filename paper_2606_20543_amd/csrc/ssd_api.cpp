@@ -786,7 +786,7 @@ int last_layer_tail(ssd_session* s, const PassShape& ps, int K, const EpiArgs& b
   for (const GemmPlan* gp : {&po, &p13, &p2})
     if (gemm_partials_floats(*gp, B) > s->gpart_cap || (size_t)gemm_counters(*gp) > s->gcnt_cap)
       throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the split-K workspace"};
-  if (gemm_parts(po, d) > s->ssq_parts_cap || gemm_parts(p2, d) > s->ssq_parts_cap)
+  if (po.n_fb > s->ssq_parts_cap || p2.n_fb > s->ssq_parts_cap)
     throw HipError{hipErrorInvalidValue, "rms partial sums exceed their buffer"};
   const ActIn in_x{(const uint16_t*)s->xn, s->xn_plane, d, 0, 1, ps.tiled(p13, B)},
       in_h{(const uint16_t*)s->h, s->h_plane, dff, 0, 1, ps.tiled(p2, B)};
@@ -807,7 +807,7 @@ int last_layer_tail(ssd_session* s, const PassShape& ps, int K, const EpiArgs& b
   e = base;
   e.kind = EPI_SWIGLU;
   e.ssq = s->ssq;
-  e.ssq_parts = gemm_parts(po, d);
+  e.ssq_parts = po.n_fb;
   e.h = s->h;
   e.tiled = in_h.tiled;
   e.ld = dff;
@@ -823,7 +823,7 @@ int last_layer_tail(ssd_session* s, const PassShape& ps, int K, const EpiArgs& b
   m->prof.run(3, (double)d * dff * es + (double)B * dff * A + (double)B * d * (8 + A), st, [&] {
     gemm_bf16(p2, W.w2, d, dff, in_h, B, e, s->gpart, s->gcnt, st);
   }, 2.0 * B * d * dff, p2.tile);
-  return gemm_parts(p2, d);
+  return p2.n_fb;
 }
 
 // lm_mode: 0 = logits for all B*K rows; 1 = logits for the last row of each sequence only.
@@ -905,7 +905,7 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       need(gemm_partials_floats(*gp, M) <= s->gpart_cap && (size_t)gemm_counters(*gp) <= s->gcnt_cap,
            "GEMM plan exceeds the split-K workspace");
     }
-    need(gemm_parts(po, d) <= s->ssq_parts_cap && gemm_parts(p2, d) <= s->ssq_parts_cap, "rms partial sums exceed their buffer");
+    need(po.n_fb <= s->ssq_parts_cap && p2.n_fb <= s->ssq_parts_cap, "rms partial sums exceed their buffer");
     need(attn_partials_floats(dm, pa, B) <= s->apart_cap && (size_t)B * dm.Hkv * pa.nqg <= s->acnt_cap,
          "attention plan exceeds its workspace");
     double attn_bytes = 2.0 * M * dm.Hq * D * A;  // q read + o written
@@ -999,7 +999,7 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       m->prof.run(1, o_bytes, st, [&] {
         gemm_bf16(po, W.wo, d, dm.Hq * D, in_o, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * d * dm.Hq * D, po.tile);
-      ssq_parts = gemm_parts(po, d);
+      ssq_parts = po.n_fb;
       e = base;
       e.kind = EPI_SWIGLU;
       e.ssq = s->ssq;
@@ -1020,7 +1020,7 @@ bool run_forward(ssd_session* s, int K, int lm_mode, const PassIo& io = PassIo{}
       m->prof.run(3, dn_bytes, st, [&] {
         gemm_bf16(p2, W.w2, d, dm.dff, in_h, M, e, s->gpart, s->gcnt, st);
       }, 2.0 * M * d * dm.dff, p2.tile);
-      ssq_parts = gemm_parts(p2, d);
+      ssq_parts = p2.n_fb;
     }
     EpiArgs e = base;
     e.kind = EPI_LOGITS;
@@ -1642,7 +1642,7 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     auto plan = [&](int N, int K) {
       GemmPlan p = gemm_plan_bf16(R, N, K, X);
       if (gemm_partials_floats(p, R) > w.gpart_cap || (size_t)gemm_counters(p) > w.gcnt_cap ||
-          (N == d && gemm_parts(p, N) > w.ssq_cap))
+          (N == d && p.n_fb > w.ssq_cap))
         throw HipError{hipErrorInvalidValue, "GEMM plan exceeds the draft head's workspace"};
       return p;
     };
@@ -1663,7 +1663,7 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     e = base;
     e.kind = EPI_SWIGLU;
     e.ssq = w.ssq;
-    e.ssq_parts = gemm_parts(p0, d);
+    e.ssq_parts = p0.n_fb;
     e.tiled = t2;
     e.ld = mi;
     gemm_bf16(p1, h->w13, 2 * mi, d, rows_of(w.xn, w.xn_plane, d, t1), R, e, w.gpart, w.gcnt, st);
@@ -1678,7 +1678,7 @@ void head_forward(ssd_draft_head* h, const HeadWork& w, int R, const float* hin,
     e = base;
     e.kind = EPI_LOGITS;
     e.ssq = w.ssq;
-    e.ssq_parts = gemm_parts(p2, d);
+    e.ssq_parts = p2.n_fb;
     e.ld = dm.Vimg;
     gemm_bf16(p3, m->wlm, dm.Vimg, d, rows_of(w.xn, w.xn_plane, d, t3), R, e, w.gpart, w.gcnt, st);
   }
@@ -1705,7 +1705,7 @@ NoallocLayout noalloc_layout(const Dims& dm, int mi, int R, int xcd) {
       GemmPlan pl = gemm_plan_bf16(R, p.first, p.second, xcd);
       l.gpart = std::max(l.gpart, gemm_partials_floats(pl, R));
       l.gcnt = std::max(l.gcnt, (size_t)gemm_counters(pl));
-      if (p.first == d) l.parts = std::max(l.parts, gemm_parts(pl, d));
+      if (p.first == d) l.parts = std::max(l.parts, pl.n_fb);
     }
   }
   const size_t r = (size_t)R;

@@ -139,8 +139,8 @@ constexpr int GEMM_RMS_MAX_PARTS = 128;
 constexpr int ROWS_MAX = 128;
 
 // GEMM launch plan for one (M, N, K) problem.  tile 0: the few-row kernel, 16 NT
-// features and 16 MT rows per workgroup, K split S ways (n_fb counts 64-feature
-// groups; see gemm_parts).
+// features and 16 MT rows per workgroup, its whole K share in one chunk.  n_fb is
+// also the count of x^2 parts per row that a residual projection writes.
 struct GemmPlan {
   int MT, NT, KCB;  // token tiles, feature tiles per wave, 32-k blocks per chunk
   int WV;           // waves per workgroup
@@ -157,14 +157,10 @@ struct GemmPlan {
   int tail_S;       //   in a second launch with K split tail_S ways (a last round that would run part empty)
   int tail_nt;      //   3: the rest as whole 128 x 192 tiles instead (tail_S 1), else 0
 };
-// feature blocks of a plan's workgroups for output width N: the x^2 parts per
-// row that a residual projection writes
-inline int gemm_parts(const GemmPlan& p, int N) { return p.tile ? p.n_fb : (N / 16 + p.NT - 1) / p.NT; }
 // arrival counters a plan uses when K is split (one per output tile)
 inline int gemm_counters(const GemmPlan& p) {
   if (p.tile && p.tail_fb) return p.tail_nt ? 0 : (p.n_fb - p.tail_fb) * p.m_tiles;
-  if (p.S <= 1) return 0;
-  return p.tile ? p.n_fb * p.m_tiles : gemm_parts(p, p.n_fb * p.bn);
+  return p.S > 1 ? p.n_fb * (p.tile ? p.m_tiles : 1) : 0;
 }
 // Row counts that cover every plan class: the few-row kernel's (up to 16, 32,
 // 48, 64, 96 and 128 rows) and each count of 128-row tiles up to 256 (a

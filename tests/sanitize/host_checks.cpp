@@ -115,11 +115,14 @@ int main() {
     for (const auto& nk : nks) {
       for (int M = 1; M <= 4352; M += (M < 160 ? 1 : 37)) {
         for (int X : {0, 8}) {
-          GemmPlan p = gemm_plan_bf16(M, nk.first, nk.second, X);
-          CHECK(p.n_fb * p.bn == nk.first);
-          CHECK(p.S >= 1);
-          CHECK(gemm_partials_floats(p, M) < ((size_t)1 << 40));
-          CHECK(gemm_counters(p) >= 0);
+          for (auto plan : {gemm_plan_bf16, gemm_plan_guided}) {
+            GemmPlan p = plan(M, nk.first, nk.second, X);
+            CHECK(p.n_fb * p.bn >= nk.first && (p.n_fb - 1) * p.bn < nk.first);
+            CHECK(p.tile == 0 || p.n_fb * p.bn == nk.first);
+            CHECK(p.S >= 1);
+            CHECK(gemm_partials_floats(p, M) < ((size_t)1 << 40));
+            CHECK(gemm_counters(p) >= 0);
+          }
         }
       }
     }

@@ -1,58 +1,24 @@
 """Host-side invariants of the bf16 GEMM launch plans (no GPU: the planner is
 host code inside libssd.so, called here through its C++ symbols).
 
-Every plan must tile its problem exactly (feature blocks x block width = N,
-splits x chunks x chunk width = K), give the tiled kernel's pipeline a stage
-count it runs (a multiple of the depth for depths 2 and 4, at least two
-stages for depth 3), and fit the workspaces that sessions
+Every plan, of common passes and of guided blocks, must tile its problem
+exactly (feature blocks x block width cover N, splits x chunks x chunk width =
+K), give the tiled kernel's pipeline a stage count it runs (a multiple of the
+depth for depths 2 and 4, at least two stages for depth 3) and the few-row
+kernel's eight waves a k-block each, and fit the workspaces that sessions
 and draft heads size once, at creation, by planning a fixed set of row
 counts: a plan for any row count must need no more split-K partials,
 arrival counters or per-row x^2 parts than the largest of that set, or a
 launch would write past its buffer.  Shapes: the projections of the 1B, 7B
 and 8B backbones and of a draft head (m = 2d), row counts 1..4352.
 """
-import ctypes
-
 import pytest
 
-import paper_2606_20543_amd as ssd
 import synth
-
-
-class GemmPlan(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int) for n in ("MT", "NT", "KCB", "WV", "S", "n_fb", "kchunks", "bn", "xcd", "tile",
-                                            "m_tiles", "depth", "tail_fb", "tail_S", "tail_nt")]
-
+from tests.plan_util import ROWS_MAX, counters, partials, plan, plan_guided, row_classes
 
 TILE_ROWS, TILE_KT = 128, 64
-RMS_MAX_PARTS = 128
-
-
-@pytest.fixture(scope="module")
-def planner():
-    L = ssd.lib()
-    plan = getattr(L, "_ZN3ssd14gemm_plan_bf16Eiiii")
-    plan.argtypes = [ctypes.c_int] * 4
-    plan.restype = GemmPlan
-    parts = getattr(L, "_ZN3ssd20gemm_partials_floatsERKNS_8GemmPlanEi")
-    parts.argtypes = [ctypes.POINTER(GemmPlan), ctypes.c_int]
-    parts.restype = ctypes.c_size_t
-    return lambda M, N, K, xcd=8: plan(M, N, K, xcd), lambda p, M: parts(ctypes.byref(p), M)
-
-
-def counters(p):
-    """Arrival counters a plan uses (split-K reductions)."""
-    if p.tile and p.tail_fb:
-        return 0 if p.tail_nt else (p.n_fb - p.tail_fb) * p.m_tiles
-    if p.tile:
-        return p.n_fb * p.m_tiles if p.S > 1 else 0
-    return p.n_fb
-
-
-def row_classes():
-    """The row counts workspaces are sized over (the planner's classes: up to
-    16, 32 and 64 rows, 65..128, then each count of 128-row tiles to 256)."""
-    return [1, 16, 17, 32, 33, 64, 65, 128] + [128 * t for t in range(2, 257)]
+PLANNERS = pytest.mark.parametrize("planner", [plan, plan_guided])
 
 
 def shapes(m):
@@ -66,11 +32,11 @@ ROWS = sorted(set(list(range(1, 300)) + list(range(300, 4353, 37)) + [512, 1024,
 
 
 @pytest.mark.parametrize("model", [synth.M1B, synth.M7B, synth.M8B], ids=["1b", "7b", "8b"])
+@PLANNERS
 def test_plans_tile_their_problem(planner, model):
-    plan, _ = planner
     for N, K in shapes(model):
         for M in ROWS:
-            p = plan(M, N, K)
+            p = planner(M, N, K)
             where = f"M={M} N={N} K={K}"
             assert p.S >= 1 and p.n_fb >= 1, where
             if p.tile == 3:
@@ -114,34 +80,38 @@ def test_plans_tile_their_problem(planner, model):
                 if p.S > 1:
                     assert p.n_fb * p.m_tiles * p.S < 512, where  # splits stop once the grid fills the CUs
             else:
+                # few-row kernel: eight waves share each split's k-blocks; 16 MT rows a launch
+                assert p.MT in (1, 2, 3, 4, 6, 8) and 16 * p.MT >= min(M, ROWS_MAX) > 16 * (p.MT - 2), where
+                assert p.NT in (1, 2, 3, 4, 6) and p.bn == 16 * p.NT, where
                 assert p.n_fb * p.bn >= N > (p.n_fb - 1) * p.bn, where
-                assert p.KCB * p.kchunks * p.S * 32 == K, where
+                assert p.KCB * p.S * 32 == K and p.kchunks == 1 and (p.S == 1 or p.KCB >= 8), where
             if N == model.d_model:
-                # consumers read at most this many per-row x^2 parts
-                assert p.n_fb <= (N + 63) // 64 <= RMS_MAX_PARTS, where
+                # the x^2 sums of a residual projection: one per row and feature block, buffers for N / 16
+                assert p.n_fb <= N // 16, where
 
 
 @pytest.mark.parametrize("model", [synth.M1B, synth.M7B, synth.M8B], ids=["1b", "7b", "8b"])
+@PLANNERS
 def test_workspace_classes_bound_every_row_count(planner, model):
-    plan, partials = planner
     for N, K in shapes(model):
-        cap_part = max(partials(plan(Mc, N, K, 0), Mc) for Mc in row_classes())
-        cap_cnt = max(counters(plan(Mc, N, K, 0)) for Mc in row_classes())
+        cap_part = max(partials(planner(Mc, N, K, 0), Mc) for Mc in row_classes())
+        cap_cnt = max(counters(planner(Mc, N, K, 0)) for Mc in row_classes())
         for M in ROWS:
             for xcd in (0, 8):
-                p = plan(M, N, K, xcd)
+                p = planner(M, N, K, xcd)
                 assert partials(p, M) <= cap_part, f"M={M} N={N} K={K}: split-K partials beyond the workspace"
                 assert counters(p) <= cap_cnt, f"M={M} N={N} K={K}: arrival counters beyond the workspace"
 
 
-def test_tiled_plan_choices(planner):
+def test_tiled_plan_choices():
     """The measured choices: 128 x 256 eight-wave tiles where each workgroup
     keeps at least 32 stages after the K split (at most 256 workgroups), else
     128-feature tiles (three weight stages) where they make at least 160
     workgroups, 64-feature tiles with four pipeline stages otherwise, K split
     until the grid reaches 256 workgroups; 128 x 192 eight-wave tiles where
-    the 256-feature grid leaves CUs idle; streaming launches up to 64 rows."""
-    plan, _ = planner
+    the 256-feature grid leaves CUs idle; the few-row
+    kernel up to 64 rows, and up to 128 where the wide tiles' modelled time is not
+    less; guided blocks of 65 to 128 rows keep the tiles."""
     m = synth.M8B
     gu = plan(512, 2 * m.d_ff, m.d_model)  # 112 x 4 = 448 tiles of 128 x 256: 256, then 192 as 256 of 128 x 192
     assert (gu.tile, gu.bn, gu.S, gu.tail_fb, gu.tail_nt, gu.tail_S) == (3, 256, 1, 64, 3, 1)
@@ -163,3 +133,9 @@ def test_tiled_plan_choices(planner):
     assert (o1.tile, o1.NT, o1.S) == (1, 2, 4)
     for M in (1, 24, 48, 64):
         assert plan(M, 2 * synth.M1B.d_ff, synth.M1B.d_model).tile == 0
+    for M in (96, 128):  # 8B: gate/up on the wide tiles, the output layer too beyond 96 rows
+        assert plan(M, 2 * m.d_ff, m.d_model).tile == 3
+        assert plan(M, m.v_img, m.d_model).tile == (3 if M > 96 else 0)
+        assert plan(M, m.d_model, m.d_ff).tile == 0
+        assert plan(M, 2 * synth.M1B.d_ff, synth.M1B.d_model).tile == 0
+        assert plan_guided(M, 2 * synth.M1B.d_ff, synth.M1B.d_model).tile == 1
