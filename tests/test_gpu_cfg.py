@@ -19,6 +19,7 @@ from oracle import decode as Dc
 from oracle import schedule as S
 from oracle import select as R
 from tests import gpu_util as G
+from tests.plan_util import plan_guided
 
 pytestmark = pytest.mark.gpu
 
@@ -151,6 +152,15 @@ def wide():
 @pytest.mark.parametrize("rule,top_k", [(R.RULE_GREEDY, 0), (R.RULE_ACCEPT_REJECT, 2000)])
 def test_guided_rounds_bf16(wide, rule, top_k):
     stats = _rounds(BF16, wide, 1, 40, ((24, 2), (5, 1)), rule, top_k)
+    print("bf16 guided max logit error", stats["max_logit_err"], flush=True)
+
+
+@pytest.mark.parametrize("rule,top_k", [(R.RULE_SAMPLE, 2000), (R.RULE_ACCEPT_REJECT, 2000)])
+def test_guided_rounds_bf16_many_rows(wide, rule, top_k):
+    """Blocks of 96 and 128 rows (two images of two streams): the tiled kernels."""
+    for M in (96, 128):
+        assert plan_guided(M, 2 * BF16.d_ff, BF16.d_model).tile == 1
+    stats = _rounds(BF16, wide, 2, 40, ((24, 1), (32, 1)), rule, top_k)
     print("bf16 guided max logit error", stats["max_logit_err"], flush=True)
 
 

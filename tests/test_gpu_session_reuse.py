@@ -1,7 +1,8 @@
 """Sessions that take over a freed session's workspace: the same bits as on a
 model that never had another session, whatever the earlier session left in it
-(larger and smaller shapes, another stream of requests, a poisoned-looking
-fill), and several live sessions at once never share one."""
+(larger and smaller shapes, other requests, NaN in every cached key and value),
+several live sessions at once never share one, and a session may be freed after
+its model."""
 import numpy as np
 import pytest
 
@@ -57,3 +58,48 @@ def test_reused_workspace_gives_the_same_bits():
             ssd.ssd_free_session(sess)
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("shape", [
+    SHAPE,
+    synth.ModelShape(2, 512, 4, 1, 128, 768, 640, 512, "bf16"),  # head dim 128: blocks of many query rows (below)
+    synth.ModelShape(2, 64, 4, 2, 16, 100, 90, 70, "f32"),
+    synth.ModelShape(2, 24, 4, 2, 6, 36, 40, 30, "f32"),  # head dim that 16-byte loads cannot take
+], ids=["bf16-64", "bf16-128", "f32-16", "f32-6"])
+@pytest.mark.parametrize("K", [3, 40])
+def test_keys_of_an_earlier_session_are_never_seen(shape, K):
+    """Token 0's embedding is NaN, so a prompt that begins with it leaves NaN keys and values in the whole workspace;
+    the next session's keys are not cleared, and must be masked without entering any sum."""
+    w = synth.weights(shape, gain_std=0.1)
+    w[:shape.d_model] = 0x7FC0 if shape.dtype == "bf16" else np.nan
+    B, P = 2, 130
+    rng = np.random.default_rng(7)
+    clean = rng.integers(1, shape.vocab, (B, P)).astype(np.int32)
+    nan = clean.copy()
+    nan[:, 0] = 0
+    blk = rng.integers(max(shape.img_lo, 1), shape.img_hi, (B, K)).astype(np.int32)
+
+    def use(model, prefix):
+        sess = ssd.ssd_prefill(model, B, P, prefix, P + 2 * K, K)
+        outs = [G.gpu_verify(sess, shape, blk, G.vparams(), want_h=True), G.gpu_verify(sess, shape, blk, G.vparams(commit=1))]
+        outs.append(G.gpu_verify(sess, shape, blk, G.vparams(1, top_k=9, rnd=1), want_h=True))
+        ssd.ssd_free_session(sess)
+        return outs
+
+    models = [ssd.ssd_init_model(G.cfg_of(shape), w) for _ in range(2)]
+    want = use(models[0], clean)
+    left = use(models[1], nan)
+    assert np.isnan(left[0]["logits"]).all() and np.isfinite(want[0]["logits"]).all()
+    got = use(models[1], clean)
+    assert all(_same(a, b) for a, b in zip(got, want))
+    for m in models:
+        ssd.ssd_free_model(m)
+
+
+def test_a_session_outlives_its_model():
+    pair = G.Pair(SHAPE, gain_std=0.1, oracle=False)
+    first, _ = _use(pair.model, 2, 70, 16, 1)
+    second, _ = _use(pair.model, 1, 70, 9, 3)
+    ssd.ssd_free_session(first)  # its workspace is kept, and freed with the model
+    pair.close()
+    ssd.ssd_free_session(second)
