@@ -157,18 +157,23 @@ class BlockPool {
   bool closed_ = false;
 };
 
-void* device_alloc(size_t bytes) {
+// alloc(&p, bytes), once more behind the release of the kept blocks when memory has run out
+template <typename Alloc>
+void* device_alloc(size_t bytes, Alloc&& alloc) {
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, bytes);
+  hipError_t e = alloc(&p, bytes);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
-    if (BlockPool::release_all()) e = hipMalloc(&p, bytes);
+    if (BlockPool::release_all()) e = alloc(&p, bytes);
   }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     throw HipError{e, "hipMalloc"};
   }
   return p;
+}
+void* device_alloc(size_t bytes) {
+  return device_alloc(bytes, [](void** p, size_t n) { return hipMalloc(p, n); });
 }
 
 struct Allocs {

@@ -1,12 +1,15 @@
 // Host-side logic of libssd under AddressSanitizer and UndefinedBehaviorSanitizer,
 // on the CPU (no GPU is touched): configuration validation and packed sizes,
 // argument checks of every entry point, GEMM launch plans and their workspace
-// sizes, the image pass plans, and the session workspace sizing.  Built with
+// sizes, the image pass plans, the session and head workspace sizing, and the
+// block pool.  Built with
 // the library's host source included into this translation unit, so the
 // internal (file-local) functions are callable; device code is not compiled.
 #include "../../paper_2606_20543_amd/csrc/ssd_api.cpp"
 
+#include <atomic>
 #include <cstdio>
+#include <thread>
 
 namespace {
 
@@ -171,6 +174,64 @@ int main() {
     s->pool = m->pool;
     ssd_free_model(m);
     ssd_free_session(s);
+  }
+  // the block a model keeps: its bound, sizes it serves, one at a time, closing, and its release when memory runs
+  // out (addresses that no device knows: the runtime refuses to free them)
+  {
+    char a[4], b[4];
+    auto pool = BlockPool::make();
+    size_t got = 0;
+    pool->set_max(1000);
+    pool->give(a, 1001);  // above the bound: not kept
+    CHECK(pool->take(1, &got) == nullptr);
+    pool->give(a, 1000);
+    CHECK(pool->take(1001, &got) == nullptr && pool->take(499, &got) == nullptr);
+    CHECK(pool->take(500, &got) == a && got == 1000);
+    CHECK(pool->take(500, &got) == nullptr);  // handed out
+    pool->give(a, 600);
+    pool->give(b, 800);  // takes a's place
+    CHECK(pool->take(600, &got) == b && got == 800 && pool->take(600, &got) == nullptr);
+    int calls = 0;
+    auto full = [&](void** p, size_t) {  // out of memory while a block is kept
+      ++calls;
+      *p = b;
+      return calls == 1 ? hipErrorOutOfMemory : hipSuccess;
+    };
+    pool->give(a, 600);
+    CHECK(device_alloc(8, full) == b && calls == 2 && pool->take(600, &got) == nullptr);
+    bool thrown = false;
+    calls = 0;
+    try {
+      device_alloc(8, full);  // nothing kept: no second try
+    } catch (HipError& e) {
+      thrown = e.e == hipErrorOutOfMemory;
+    }
+    CHECK(thrown && calls == 1);
+    pool->give(a, 600);
+    pool->close();
+    CHECK(pool->take(600, &got) == nullptr);
+    pool->give(b, 600);  // a session freed after its model
+    CHECK(pool->take(600, &got) == nullptr);
+    // models and sessions of several threads; a block is never with two owners
+    auto shared = BlockPool::make();
+    shared->set_max(1000);
+    std::atomic<int> owners{0}, twice{0};
+    shared->give(a, 600);
+    std::vector<std::thread> ts;
+    for (int t = 0; t < 4; ++t)
+      ts.emplace_back([&] {
+        for (int i = 0; i < 2000; ++i) {
+          size_t n = 0;
+          auto own = BlockPool::make();
+          if (void* p = shared->take(500, &n)) {
+            if (owners.fetch_add(1) != 0) ++twice;
+            owners.fetch_sub(1);
+            shared->give(p, n);
+          }
+        }
+      });
+    for (auto& t : ts) t.join();
+    CHECK(twice == 0 && shared->take(500, &got) == a);
   }
   // 7. the allocation-free head run takes every size whose staged inputs, activations, logits and one set of
   // x^2 sums fit the static array, as long as the split-K partials of its GEMMs fit beside them: sizes at that

@@ -2,8 +2,8 @@
 UndefinedBehaviorSanitizer, on the CPU: tests/sanitize/host_checks.cpp includes
 the host source of libssd and exercises configuration validation, argument
 checks of every entry point, GEMM launch plans and their workspace sizes, the
-image pass plans (against the printed pass-count formula) and the session
-workspace sizing.  Only host code is instrumented (-Xarch_host); no GPU is
+image pass plans (against the printed pass-count formula), the session and head
+workspace sizing, and the block pool that models keep between sessions.  Only host code is instrumented (-Xarch_host); no GPU is
 touched.  Any sanitizer report or failed check fails the test."""
 import concurrent.futures as cf
 import os
