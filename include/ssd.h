@@ -116,8 +116,9 @@ ssd_status ssd_prefill(ssd_model* model, int32_t B, int32_t P, const int32_t* pr
 
 /* Waits for the session's work.  May be called after the model has been freed
  * (no other call on the session may).  The workspace (if at most 1/32 of the GPU's
- * memory, and one per model) stays with the model for its next session; it is
- * freed with the model, or when an allocation of the library needs the memory. */
+ * memory, one per model, and while 1/8 of the memory is free) stays with the
+ * model for its next session; it is freed with the model, or when an allocation
+ * of the library needs the memory. */
 void ssd_free_session(ssd_session* sess);
 
 typedef struct {

@@ -69,10 +69,13 @@ bool is_device_ptr(const void* p) {
 // session freed last, which the next session of about the same size takes over
 // (mapping and unmapping gigabytes costs milliseconds: 8 sequences of 4352
 // positions on a two-layer 8B model, 1.3 GB, 0.3 ms to allocate and 3.4 ms
-// to free).  Bounded by max_bytes, freed with the model, and released when any
-// allocation of the library runs out of memory.  A block comes in only after
-// its session's stream has drained.  Held jointly with the sessions, so a
-// session freed after its model still finds it (closed).
+// to free).  Kept up to 1/32 of the GPU's memory (9 GB: the decode workspace of
+// the 32-layer 8B model fits) and only while 1/8 of it is free, so that a
+// process that needs the memory elsewhere gets it as its sessions end (asking
+// takes 2.5 us); freed with the model, and released when any allocation of the
+// library runs out of memory.  A block comes in only after its session's stream
+// has drained.  Held jointly with the sessions, so a session freed after its
+// model still finds it (closed).
 class BlockPool {
  public:
   static std::shared_ptr<BlockPool> make() {
@@ -91,20 +94,24 @@ class BlockPool {
     block_ = nullptr;
     return p;
   }
-  // keep an idle block (its owner's work has finished); a kept one makes room
-  void give(void* p, size_t bytes) {
-    void* out = p;
+  // keep an idle block (its owner's work has finished) on a GPU of total_b bytes,
+  // free_b of them free; a kept one makes room, and goes as well where memory is short
+  void give(void* p, size_t bytes, size_t free_b, size_t total_b) {
+    void* out[2] = {p, nullptr};
     {
       std::lock_guard<std::mutex> lk(mu_);
-      if (!closed_ && bytes <= max_bytes_) {
-        out = block_;
+      if (free_b < total_b / 8) {
+        out[1] = block_;
+        block_ = nullptr;
+      } else if (!closed_ && bytes <= total_b / 32) {
+        out[0] = block_;
         block_ = p;
         size_ = bytes;
       }
     }
-    if (out) (void)hipFree(out);
+    for (void* o : out)
+      if (o) (void)hipFree(o);
   }
-  void set_max(size_t bytes) { max_bytes_ = bytes; }
   void close() {
     {
       std::lock_guard<std::mutex> lk(mu_);
@@ -153,7 +160,7 @@ class BlockPool {
   }
   std::mutex mu_;
   void* block_ = nullptr;
-  size_t size_ = 0, max_bytes_ = 0;
+  size_t size_ = 0;
   bool closed_ = false;
 };
 
@@ -1471,9 +1478,6 @@ ssd_status ssd_init_model(const ssd_model_config* cfg, const void* weights, void
     off += (size_t)dm.V * d;
     if ((int64_t)off != numel_of(*cfg)) throw HipError{hipErrorInvalidValue, "layout size mismatch"};
     HIPCHK(hipStreamSynchronize(st));
-    size_t free_b = 0, total_b = 0;
-    HIPCHK(hipMemGetInfo(&free_b, &total_b));
-    m->pool->set_max(total_b / 32);  // 9 GB: the 32-layer 8B model's decode workspace fits
     m->scratch = scratch_of_current_device();  // set-up of the allocation-free head runs
   } catch (HipError& e) {
     delete m;
@@ -1491,7 +1495,12 @@ void ssd_free_session(ssd_session* s) {
   // a session that no caller holds)
   // the workspace stays with the model once the session's work has finished
   if (hipStreamSynchronize(s->stream) == hipSuccess && !s->poisoned && s->pool) {
-    s->pool->give(s->block, s->block_bytes);
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+      (void)hipGetLastError();
+      total_b = 0;
+    }
+    s->pool->give(s->block, s->block_bytes, free_b, total_b);
     s->block = nullptr;
   }
   delete s;

@@ -181,23 +181,30 @@ int main() {
     char a[4], b[4];
     auto pool = BlockPool::make();
     size_t got = 0;
-    pool->set_max(1000);
-    pool->give(a, 1001);  // above the bound: not kept
+    auto give = [&](void* p, size_t bytes) { pool->give(p, bytes, 4000, 32000); };
+    give(a, 1001);  // above the bound: not kept
     CHECK(pool->take(1, &got) == nullptr);
-    pool->give(a, 1000);
+    pool->give(a, 1000, 3999, 32000);  // memory is short
+    CHECK(pool->take(1, &got) == nullptr);
+    pool->give(a, 1000, 0, 0);  // memory unknown
+    CHECK(pool->take(1, &got) == nullptr);
+    give(a, 1000);
     CHECK(pool->take(1001, &got) == nullptr && pool->take(499, &got) == nullptr);
     CHECK(pool->take(500, &got) == a && got == 1000);
     CHECK(pool->take(500, &got) == nullptr);  // handed out
-    pool->give(a, 600);
-    pool->give(b, 800);  // takes a's place
+    give(a, 600);
+    give(b, 800);  // takes a's place
     CHECK(pool->take(600, &got) == b && got == 800 && pool->take(600, &got) == nullptr);
+    give(a, 600);
+    pool->give(b, 600, 3999, 32000);  // memory is short: the kept one goes too
+    CHECK(pool->take(600, &got) == nullptr);
     int calls = 0;
     auto full = [&](void** p, size_t) {  // out of memory while a block is kept
       ++calls;
       *p = b;
       return calls == 1 ? hipErrorOutOfMemory : hipSuccess;
     };
-    pool->give(a, 600);
+    give(a, 600);
     CHECK(device_alloc(8, full) == b && calls == 2 && pool->take(600, &got) == nullptr);
     bool thrown = false;
     calls = 0;
@@ -207,16 +214,15 @@ int main() {
       thrown = e.e == hipErrorOutOfMemory;
     }
     CHECK(thrown && calls == 1);
-    pool->give(a, 600);
+    give(a, 600);
     pool->close();
     CHECK(pool->take(600, &got) == nullptr);
-    pool->give(b, 600);  // a session freed after its model
+    give(b, 600);  // a session freed after its model
     CHECK(pool->take(600, &got) == nullptr);
     // models and sessions of several threads; a block is never with two owners
     auto shared = BlockPool::make();
-    shared->set_max(1000);
     std::atomic<int> owners{0}, twice{0};
-    shared->give(a, 600);
+    shared->give(a, 600, 4000, 32000);
     std::vector<std::thread> ts;
     for (int t = 0; t < 4; ++t)
       ts.emplace_back([&] {
@@ -226,7 +232,7 @@ int main() {
           if (void* p = shared->take(500, &n)) {
             if (owners.fetch_add(1) != 0) ++twice;
             owners.fetch_sub(1);
-            shared->give(p, n);
+            shared->give(p, n, 4000, 32000);
           }
         }
       });
