@@ -26,6 +26,12 @@
  *    one given to ssd_init_model and is never replaced.
  *  - The caller owns every array it passes; the library owns the device
  *    weights, the KV cache and all workspaces of a model/session.
+ *  - Kernels of a verify step or a head run read and write device arrays of the
+ *    library's GPU in place (logits and states 16-byte aligned, the whole array
+ *    inside one allocation; others are staged): output arrays change while the
+ *    call's work runs, may hold part of a result after SSD_E_DEVICE, and must
+ *    not overlap another array of the call (but logits_out may be the
+ *    ref_logits array, and a head run's drafts its tokens).
  *  - Token ids are vocabulary ids.  Image codes occupy [img_lo, img_hi);
  *    every block (draft) token must lie in that range.  Logits cover only the
  *    image range, in code order.

@@ -23,13 +23,14 @@
 // and 233.5 -> 142; 8B widths at 48 rows 238 -> 155.
 //
 // 65 to 128 rows: four waves for each half of the rows (48 or 64), every K share
-// read by one wave of each.  All CUs together draw the token rows and weights
-// through the L2s at their limit (about 66 GB/s a CU), so a launch costs the
-// bytes of its workgroups: plain weight loads, which the second row group may
-// find in L1, and feature blocks no wider than the row groups' accumulators.
+// read by one wave of each.  A launch costs the bytes its workgroups draw
+// through the L2s (its times over feature widths and splits fit 66 GB/s a CU
+// with all CUs drawing: a fit, not a counter), hence plain weight loads, which
+// the second row group may find in L1, and feature blocks no wider than the row
+// groups' accumulators.
 // Against the 128 x 64 tiles with LDS stages that ran these rows, 96 and 128
-// rows: a 1B layer without attention 99.6 -> 71 and 104.4 -> 75 us, a 7B layer
-// 223.8 -> 158 and 234.7 -> 185, 8B QKV 36 -> 27 and 37.6 -> 31.5.
+// rows: a 1B layer without attention 97.8 -> 69.7 and 103 -> 80 us, a 7B layer
+// 222 -> 155 and 232 -> 182, 8B QKV 35 -> 26.9 and 37.2 -> 30.3.
 #pragma once
 
 #include "tiles.h"

@@ -962,10 +962,11 @@ GemmPlan gemm_plan_bf16(int M, int N, int K, int xcd) {
     // one 128-row tile: the few-row kernel with two row groups, or the 128 x 256
     // tiles where their modelled time is less (8 us, 1.4 us a 64-input stage, whose
     // weights come from HBM here, and 0.43 us a MB of partial sums out and back).
-    // At 128 rows of the 8B widths: gate/up 78 us on the tiles, 99 on the few-row
-    // kernel; output layer 87 and 101; but QKV 38 (64-feature tiles) and 31.5.  1B
-    // widths, on the 64-feature tiles and here: QKV 27.1 -> 19.6, O 16.1 -> 12, gate/up
-    // 33.3 -> 21.4, down 27.9 -> 18.1 us.
+    // At 128 rows of the 8B widths: gate/up 77 us on the tiles, 99 on the few-row
+    // kernel; output layer 86 and 101; but QKV 37 (64-feature tiles) and 30.  1B
+    // widths at 96 and 128 rows, on the 64-feature tiles and here: QKV 24.5 ->
+    // 18.8 and 25.7 -> 21.4 us, O 15.4 -> 11.3 and 15.8 -> 12.7, gate/up 31.1 ->
+    // 21.5 and 33.0 -> 25.3, down 26.8 -> 18.1 and 28.5 -> 20.6.
     double ns;
     const GemmPlan r = gemm_rows_plan(M, N, K, xcd, &ns);
     const GemmPlan t = gemm_plan_tiles(M, N, K, xcd);

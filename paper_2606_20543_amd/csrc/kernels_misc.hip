@@ -261,7 +261,7 @@ __device__ int block_argmax(const float* row, int V, SelShared& sh) {
 // with every pass reading the row again); two 24-token rows, rule B: 151 -> 25.
 constexpr int SMP_T = 1024, SMP_W = SMP_T / 64;
 constexpr int SMP_LIST = 4096;
-constexpr int SMP_HELD = 256 * SMP_W;  // codes a workgroup holds in registers per group of a wave
+constexpr int SMP_HELD = 256 * SMP_W;  // codes a workgroup holds per group of a wave
 constexpr int SMP_BINS = 2048;
 
 struct SmpShared {
@@ -296,8 +296,9 @@ __device__ __forceinline__ Quad load_quad(const float* row, int v, int V, bool v
 }
 
 // The segment of this wave, in groups of 256 codes (four per lane).  NG > 0:
-// read once and held in registers (rows of up to 4096 NG codes: the kept set
-// takes five passes over them); NG = 0: read again by every pass.
+// read once and held (rows of up to 4096 NG codes: the kept set takes five
+// passes over them), in registers and, with 128 of them a lane, 48 (NG = 4) or
+// 180 (NG = 8) bytes of scratch; NG = 0: read again by every pass.
 template <int NG>
 struct Seg {
   const float* row;
