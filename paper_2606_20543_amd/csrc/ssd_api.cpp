@@ -72,10 +72,11 @@ bool is_device_ptr(const void* p) {
 // to free).  Kept up to 1/32 of the GPU's memory (9 GB: the decode workspace of
 // the 32-layer 8B model fits) and only while 1/8 of it is free, so that a
 // process that needs the memory elsewhere gets it as its sessions end (asking
-// takes 2.5 us); freed with the model, and released when any allocation of the
-// library runs out of memory.  A block comes in only after its session's stream
-// has drained.  Held jointly with the sessions, so a session freed after its
-// model still finds it (closed).
+// takes up to 10 us: done while the prompt pass runs, and again at the end of a
+// session older than 50 ms); freed with the model, and released when any
+// allocation of the library runs out of memory.  A block comes in only after its
+// session's stream has drained.  Held jointly with the sessions, so a session
+// freed after its model still finds it (closed).
 class BlockPool {
  public:
   static std::shared_ptr<BlockPool> make() {
@@ -428,6 +429,15 @@ struct ssd_session {
   std::shared_ptr<BlockPool> pool;   // the model's
   void* block = nullptr;             // every array below that a session starts with
   size_t block_bytes = 0;
+  size_t mem_free = 0, mem_total = 0;                   // the GPU's memory when last asked for
+  std::chrono::steady_clock::time_point mem_asked{};
+  void ask_memory() {
+    mem_asked = std::chrono::steady_clock::now();
+    if (hipMemGetInfo(&mem_free, &mem_total) != hipSuccess) {
+      (void)hipGetLastError();
+      mem_free = mem_total = 0;
+    }
+  }
   ~ssd_session() {
     if (block) (void)hipFree(block);
   }
@@ -1495,12 +1505,8 @@ void ssd_free_session(ssd_session* s) {
   // a session that no caller holds)
   // the workspace stays with the model once the session's work has finished
   if (hipStreamSynchronize(s->stream) == hipSuccess && !s->poisoned && s->pool) {
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
-      (void)hipGetLastError();
-      total_b = 0;
-    }
-    s->pool->give(s->block, s->block_bytes, free_b, total_b);
+    if (std::chrono::steady_clock::now() - s->mem_asked > std::chrono::milliseconds(50)) s->ask_memory();
+    s->pool->give(s->block, s->block_bytes, s->mem_free, s->mem_total);
     s->block = nullptr;
   }
   delete s;
@@ -1540,6 +1546,7 @@ ssd_status ssd_prefill(ssd_model* m, int32_t B, int32_t P, const int32_t* prefix
   try {
     HIPCHK(hipMemcpyAsync(s->tok, host.data(), host.size() * 4, hipMemcpyHostToDevice, s->stream));
     prefill_pass(s);
+    s->ask_memory();  // (the host would wait for the pass now)
     fwd_abort_fetch(s);
     HIPCHK(hipStreamSynchronize(s->stream));
     fwd_abort_check(s);
