@@ -372,8 +372,9 @@ void ssd_free_draft_head(ssd_draft_head* head);
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * computation and results as ssd_draft_head_run, with the run's workspace
- * (staged inputs, activations, x^2 partial sums, draft logits, split-K
- * partials and their counters) taken from a static device array of 64 MiB
+ * (staged inputs and, in their place once read, x^2 partial sums; activations,
+ * draft logits, split-K partials and their counters) taken from a static device
+ * array of 64 MiB
  * that every GPU the library runs on holds until the process ends, instead of
  * the head's own workspace.  Allocates nothing, never synchronizes, and takes
  * device arrays only (h, tokens, drafts, logits_out; SSD_E_INVAL otherwise).
