@@ -1,8 +1,11 @@
 """Sessions that take over a freed session's workspace: the same bits as on a
 model that never had another session, whatever the earlier session left in it
 (larger and smaller shapes, other requests, NaN in every cached key and value),
-several live sessions at once never share one, and a session may be freed after
-its model."""
+several live sessions at once never share one, threads may create and free them,
+and a session may be freed after its model."""
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 
@@ -15,10 +18,10 @@ pytestmark = pytest.mark.gpu
 SHAPE = synth.ModelShape(2, 512, 8, 2, 64, 768, 640, 512, "bf16")
 
 
-def _use(model, B, P, K, seed):
+def _use(model, B, P, K, seed, stream=None):
     prefix = synth.prompt(SHAPE, B, P, seed=seed).astype(np.int32)
     block = (synth.random_codes(SHAPE, (B, K), seed=seed) + SHAPE.img_lo).astype(np.int32)
-    sess = ssd.ssd_prefill(model, B, P, prefix, P + 4 * K, K)
+    sess = ssd.ssd_prefill(model, B, P, prefix, P + 4 * K, K, stream)
     carry = np.zeros((B, SHAPE.v_img), np.float32)
     ssd.ssd_get_carry(sess, carry)
     outs = [carry]
@@ -103,3 +106,42 @@ def test_a_session_outlives_its_model():
     ssd.ssd_free_session(first)  # its workspace is kept, and freed with the model
     pair.close()
     ssd.ssd_free_session(second)
+
+
+def test_threads_with_streams_of_their_own():
+    """Sessions of one model created, used and freed by three threads, each on its own stream: whichever takes the
+    kept workspace gets the bits of a session that shares with nobody."""
+    hip = G.DeviceArray.hip()
+    uses = [(2, 70, 16, 1), (1, 70, 9, 3), (3, 90, 24, 5)]
+    pair = G.Pair(SHAPE, gain_std=0.1, oracle=False)
+    want, wrong, streams = [], [], []
+    try:
+        for u in uses:
+            sess, outs = _use(pair.model, *u)
+            ssd.ssd_free_session(sess)
+            want.append(outs)
+        for _ in uses:
+            s = ctypes.c_void_p()
+            assert hip.hipStreamCreate(ctypes.byref(s)) == 0
+            streams.append(s)
+
+        def work(i):
+            try:
+                for _ in range(8):
+                    sess, outs = _use(pair.model, *uses[i], stream=streams[i].value)
+                    ssd.ssd_free_session(sess)
+                    if not all(_same(a, b) for a, b in zip(outs, want[i])):
+                        wrong.append(uses[i])
+            except Exception as e:  # noqa: BLE001 (reported by the assertion below)
+                wrong.append(e)
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(len(uses))]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not wrong
+    finally:
+        pair.close()
+        for s in streams:
+            hip.hipStreamDestroy(s)
